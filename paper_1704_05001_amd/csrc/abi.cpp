@@ -346,8 +346,9 @@ nair_status nair_get_level(nair_hier h, int32_t lvl, nair_level_view *v) {
         hipMemcpy(v->margin, L.margin.get(), sizeof(v->margin), hipMemcpyDeviceToHost) != hipSuccess)
         return bad(h, "reading the decision-margin counts failed");
     v->sweep_nnzb = -1;
-    if (L.sweep.on && hipMemcpy(&v->sweep_nnzb, L.sweep.rowptr.get() + L.sweep.nF, sizeof(int32_t),
-                                hipMemcpyDeviceToHost) != hipSuccess)
+    const int *copied = L.split.on ? L.split.rowptr.get() + 2 * static_cast<int64_t>(L.split.nF)
+                                   : (L.sweep.on ? L.sweep.rowptr.get() + L.sweep.nF : nullptr);
+    if (copied && hipMemcpy(&v->sweep_nnzb, copied, sizeof(int32_t), hipMemcpyDeviceToHost) != hipSuccess)
         return bad(h, "reading the sweep copy's size failed");
     if (L.face.on) {
         v->face_rmax = L.face.rmax;

@@ -417,6 +417,70 @@ void build_sweep(const DevBSR &A, const FaceCopy &F, const double *dinv, const i
                  hipStream_t s, bool trans, const uint32_t *amask = nullptr);
 void sweep_to_float(SweepCopy &S, int bs, hipStream_t s);
 
+// ----------------------------------------------------------- split sweeps
+// The nu F sweeps of a cycle visit on a level of at least kFewLanes lanes.  All
+// of them see the same r and the same e on C points, so with
+//   s_I = r_I - sum_{J in C} A_IJ e_J,   t_I = s_I - sum_{J in F, J != I} A_IJ e_J
+// only t changes from sweep to sweep, and it changes only on the rows U_I where
+// some F-F block of row I has a nonzero row (an upwind DG row: the nodes on the
+// faces towards F cells).  D_I^{-1} t is summed over the columns outside U_I
+// first, then over those of U_I, each in ascending order in one fma chain: the
+// value after the first part, w_I, does not change either.  So the first sweep
+// reads the whole row and keeps s and w; the later ones read the F-F blocks,
+// s, w and the U columns of D^{-1} only, and only on the rows that still change:
+// a row with no F-F block is final after the first sweep, one whose F
+// neighbours are all final after the second.
+// The F list is in descending depth (rows of depth >= 2, then 1, then 0; depth
+// = the longest chain of F-F couplings that ends in the row, cut at 2), so each
+// sweep takes a prefix of it.
+// Row f of the list (I = flist[f]) keeps its blocks in columns outside F at
+// positions rowptr[f] .. rowptr[f+1]-1 and those in F columns (not the
+// diagonal) at rowptr[nF+f] .. rowptr[nF+f+1]-1, each in ascending column order,
+// by their nonzero rows or (rc > 0) as the face copy's masks and rectangles.
+// Q4, 512 x 512 cells, three sweeps: 36% / 14% of level 0's F rows have depth >=
+// 1 / 2 (70% / 52% on level 1, 80-90% below), 9 of 25 columns are in U_I; the
+// interpolation and the sweeps of the 8 levels went from 2.01 to 1.33 ms per
+// iteration against sweeps that read every row whole.  Levels below kFewLanes
+// lanes are bound by launches and latency and keep the plain sweeps.
+struct SplitCopy {
+    bool on = false;
+    int nF = 0, n1 = 0, n2 = 0;      // F rows; rows of depth >= 1, >= 2
+    int cmax = 0, rc = 0;
+    int64_t cap = 0;                 // blocks allocated
+    DBuf<int> rowptr;                // [2 nF + 1]
+    DBuf<int> colidx, ccol;          // fine column; its coarse index through the one-point map (-1: none)
+    DBuf<uint64_t> meta;
+    DBuf<double> vals;
+    DBuf<float> vals32;
+    RowBlocks rows;
+    DBuf<uint32_t> umask;            // [nF] U_I
+    DBuf<double> dinv;               // [nF][bs][bs]: column by column, the columns outside U_I first
+    DBuf<double> s, w;               // [n1][bs], in list order
+};
+// Class of each F row (depth, cut at 2) and the F list in descending depth:
+// flist is replaced; counts (device, 2 ints) receives {n2, n1}.
+void order_by_depth(const DevBSR &A, const int8_t *cf, DBuf<int> &flist, int nF, int *counts, hipStream_t s);
+// Build S from A (and its face copy F when F.on), the depth-ordered F list and
+// its counts; amask as for build_sweep.  S.on stays false when the kept rows
+// exceed int32 offsets.
+void build_split(const DevBSR &A, const FaceCopy &F, const double *dinv, const int8_t *cf, const int *pmap,
+                 const int *flist, int nF, int n1, int n2, SplitCopy &S, hipStream_t s, const uint32_t *amask);
+void split_to_float(SplitCopy &S, int bs, hipStream_t s);
+
+template <typename MT>
+struct SplitView {
+    const int *flist = nullptr;
+    int nF = 0, n1 = 0;
+    const int *rowptr = nullptr, *colidx = nullptr, *ccol = nullptr;
+    const uint64_t *meta = nullptr;   // face rectangles when non-null
+    const MT *vals = nullptr;
+    int cmax = 0, rc = 0;
+    RowBlockView<MT> rows{};          // else the blocks by their nonzero rows
+    const uint32_t *umask = nullptr;
+    const double *dinv = nullptr;
+    double *s = nullptr, *w = nullptr;
+};
+
 template <typename MT>
 struct SweepView {
     const int *rowptr = nullptr, *colidx = nullptr;
@@ -473,10 +537,22 @@ __device__ inline bool live(const Gate &g, int row) {
 template <typename MT, typename VT>
 void launch_residual(const MatView<MT> &A, const VT *b, const VT *x, VT *r, float *r_lo, hipStream_t s,
                      Gate g = Gate());
-// Jacobi sweep over `list` rows (list == nullptr: all rows; then rows with cf != only_cf are copied)
+// Jacobi sweep over `list` rows (list == nullptr: all rows; then rows with cf != only_cf are copied).
+// split (forward F sweeps over a list, A read without a sweep copy): the sums in the order of the split
+// sweeps (see SplitCopy), bit for bit at one lane group per row
 template <typename MT, typename VT>
 void launch_relax(const MatView<MT> &A, const double *dinv, bool dinv_trans, const VT *r, const VT *ein, VT *eout,
-                  const int *list, int nlist, const int8_t *cf, int only_cf, hipStream_t s, Gate g = Gate());
+                  const int *list, int nlist, const int8_t *cf, int only_cf, hipStream_t s, Gate g = Gate(),
+                  bool split = false);
+// First split sweep, from e = P e_c: e1_F (and e2_F on the rows of depth 0; e2 nullable), s and w on the
+// others, and efin_C = e_c on the nc C rows.  groups: lane groups per row (0: from the row length)
+template <typename MT, typename VT>
+void launch_split_first(const SplitView<MT> &S, int bs, int64_t nnzb, int nb, int groups, const VT *r, const VT *ec,
+                        VT *e1, VT *e2, const int *cpts, int nc, VT *efin, hipStream_t s, Gate g = Gate());
+// A later split sweep: rows [0, n) of the list from ein to eout; rows [n, ncopy) copied
+template <typename MT, typename VT>
+void launch_split_next(const SplitView<MT> &S, int bs, int64_t nnzb, int nb, int groups, int n, int ncopy,
+                       const VT *ein, VT *eout, hipStream_t s, Gate g = Gate());
 // The first transposed F sweep from a zero guess: e1_F = D_F^{-T} r_F, other rows 0 in e0 and e1
 template <typename VT>
 void launch_relax_T_first(const double *dinv, const VT *r, const int8_t *cf, VT *e0, VT *e1, int nb, int bs,

@@ -139,7 +139,9 @@ __device__ inline double face_diag_dot(const FaceView<MT> &F, int I, int a, int 
 // order; NODIAG: the blocks hold no diagonal block, as in a sweep copy)
 constexpr int kFaceUnroll = 8;   // face rectangles up to this many columns take the unrolled row
 
-template <int BS, typename MT, typename VT, bool SKIP = false, bool PRE = false, bool NODIAG = false>
+// NEG: a block in a negative column is left out (its vector block is zero)
+template <int BS, typename MT, typename VT, bool SKIP = false, bool PRE = false, bool NODIAG = false,
+          bool NEG = false>
 __device__ inline double row_part_face(const int *__restrict__ colidx, const FaceView<MT> &F, int lo, int hi, int g,
                                        int G, int a, int I, int bs_rt, const VT *__restrict__ x, double pre = 0.0) {
     const int bs = Bs<BS>::get(bs_rt);
@@ -170,7 +172,7 @@ __device__ inline double row_part_face(const int *__restrict__ colidx, const Fac
             else acc += face_diag_dot<BS, MT, VT>(F, I, a, bs, x);
         } else {
             const uint32_t rm = static_cast<uint32_t>(m);
-            if ((rm >> a) & 1u) {
+            if (((rm >> a) & 1u) && (!NEG || J >= 0)) {
                 const uint32_t cm = static_cast<uint32_t>(m >> 32);
                 const MT *row = F.vals + static_cast<int64_t>(t) * F.rc + __popc(rm & ((1u << a) - 1u)) * F.cmax;
                 double p0 = 0.0, p1 = 0.0;
@@ -218,7 +220,7 @@ __device__ inline double row_part_face(const int *__restrict__ colidx, const Fac
 // block t's row a, when nonzero, is bs entries at vals[off[t] + rank(a) * bs],
 // summed exactly as row_part sums it; a zero row's products are exact zeros
 // and are left out, so for finite x the result equals row_part's bit for bit.
-template <int BS, typename MT, typename VT>
+template <int BS, typename MT, typename VT, bool NEG = false>
 __device__ inline double row_part_rows(const int *__restrict__ colidx, const RowBlockView<MT> &R, int lo, int hi,
                                        int g, int G, int a, int bs_rt, const VT *__restrict__ x) {
     const int bs = Bs<BS>::get(bs_rt);
@@ -239,7 +241,9 @@ __device__ inline double row_part_rows(const int *__restrict__ colidx, const Row
             mn = R.mask[tn];
             on = R.off[tn];
         }
-        if ((m >> a) & 1u) acc += block_row_dot<BS>(R.vals + o + __popc(m & below) * bs, x + static_cast<int64_t>(J) * bs, bs);
+        if (((m >> a) & 1u) && (!NEG || J >= 0))
+            acc += block_row_dot<BS>(R.vals + o + __popc(m & below) * bs, x + static_cast<int64_t>(J) * bs,
+                                     bs);
         if (tn >= hi) break;
         t = tn;
         J = Jn;
@@ -428,6 +432,49 @@ __global__ __launch_bounds__(kThreads) void k_residual(const int *__restrict__ r
     }
 }
 
+// Row I's product with x in two parts: over the columns outside F and over the
+// F columns other than I (sC, sF); nz: whether an F-F block is nonzero in row a.
+template <int BS, bool FACE, typename MT, typename VT>
+__device__ inline void row_product_split(const int *__restrict__ colidx, const MT *__restrict__ vals,
+                                         const FaceView<MT> &F, const int8_t *__restrict__ cf, int lo, int hi, int g,
+                                         int G, int a, int I, int bs_rt, const VT *__restrict__ x, double &sC,
+                                         double &sF, bool &nz) {
+    const int bs = Bs<BS>::get(bs_rt);
+    for (int t = lo + g; t < hi; t += G) {
+        const int J = colidx[t];
+        if (J == I) continue;
+        const bool inF = cf[J] == 0;
+        double d;
+        bool z = false;
+        if constexpr (FACE) {
+            d = row_part_face<BS, MT, VT, false, false, true>(colidx, F, t, t + 1, 0, 1, a, I, bs, x);
+            z = (static_cast<uint32_t>(F.meta[t]) >> a) & 1u;
+        } else {
+            const MT *blk = vals + (static_cast<int64_t>(t) * bs + a) * bs;
+            d = block_row_dot<BS>(blk, x + static_cast<int64_t>(J) * bs, bs);
+            for (int c = 0; c < bs; ++c) z = z || blk[c] != MT(0);
+        }
+        if (inF) {
+            sF += d;
+            nz = nz || z;
+        } else {
+            sC += d;
+        }
+    }
+}
+
+// D_I^{-1} t for scalar row a as the split sweeps sum it: the columns outside u
+// in one fma chain, then those of u (D row-major).
+template <int BS>
+__device__ inline double apply_dinv_split(const double *__restrict__ D, const double *t, int a, int bs, uint32_t u) {
+    double d = 0.0;
+    for (int c = 0; c < bs; ++c)
+        if (!((u >> c) & 1u)) d = __builtin_fma(D[a * bs + c], t[c], d);
+    for (int c = 0; c < bs; ++c)
+        if ((u >> c) & 1u) d = __builtin_fma(D[a * bs + c], t[c], d);
+    return d;
+}
+
 // One Jacobi sweep over the listed rows (list == nullptr: rows with cf == only_cf;
 // the other rows copy e_in): e_out_I = D_I^{-1} (r_I - sum_{J != I} A_IJ e_in_J),
 // or with D_I^{-T} (TRANS: the sweeps of the transposed cycle, with A^T's
@@ -583,6 +630,201 @@ __global__ __launch_bounds__(kThreads) void k_relax_T(const int *__restrict__ ro
                                                      FaceView<MT> face) {
     relax_rows<BS, MT, VT, true, FACE>(rowptr, colidx, vals, dinv, nb, bs_rt, G, r, ein, eout, list, nlist, cf,
                                        only_cf, gate, face);
+}
+
+// The F sweep over a list read from A itself, summed as the split sweeps sum it
+// (levels of at least kFewLanes lanes without copies): every sweep forms s, U,
+// w and t anew.
+template <int BS, typename MT, typename VT, bool FACE = false>
+__global__ __launch_bounds__(kThreads) void k_relax_split(const int *__restrict__ rowptr,
+                                                         const int *__restrict__ colidx, const MT *__restrict__ vals,
+                                                         const double *__restrict__ dinv, int bs_rt, int G,
+                                                         const VT *__restrict__ r, const VT *__restrict__ ein,
+                                                         VT *__restrict__ eout, const int *__restrict__ list,
+                                                         int nlist, const int8_t *__restrict__ cf, Gate gate,
+                                                         FaceView<MT> face) {
+    __shared__ double part[kThreads];
+    __shared__ double tb[kThreads];
+    __shared__ uint32_t um[kThreads];
+    const int bs = Bs<BS>::get(bs_rt);
+    const Lane L = lane_of(G, bs);
+    const int idx = blockIdx.x * (kThreads / (G * bs)) + L.lr;
+    int I = -1;
+    if (L.valid && idx < nlist) I = list[idx];
+    if (I >= 0 && !live(gate, I)) I = -1;
+    um[threadIdx.x] = 0u;
+    __syncthreads();
+    double sC = 0.0, sF = 0.0;
+    bool nz = false;
+    if (I >= 0) {
+        row_product_split<BS, FACE>(colidx, vals, face, cf, rowptr[I], rowptr[I + 1], L.g, G, L.a, I, bs, ein, sC, sF,
+                                    nz);
+        if (nz) atomicOr(&um[L.lr], 1u << L.a);
+    }
+    sC = reduce_groups(sC, L, G, bs, part);
+    __syncthreads();   // (part is used again)
+    sF = reduce_groups(sF, L, G, bs, part);
+    const int64_t o = static_cast<int64_t>(I) * bs + L.a;
+    if (I >= 0 && L.g == 0) tb[L.lr * bs + L.a] = (static_cast<double>(r[o]) - sC) - sF;
+    __syncthreads();
+    if (I >= 0 && L.g == 0)
+        eout[o] = static_cast<VT>(apply_dinv_split<BS>(dinv + static_cast<int64_t>(I) * bs * bs, tb + L.lr * bs, L.a,
+                                                       bs, um[L.lr]));
+}
+
+// Rows of C: efin = e_c (the interpolation's identity rows), by the workgroups of a split first sweep past its F rows'.
+template <typename VT>
+__device__ inline void split_c_rows(int64_t g, const VT *__restrict__ ec, const int *__restrict__ cpts, int nc, int bs,
+                                    VT *__restrict__ efin, const Gate &gate) {
+    if (g >= static_cast<int64_t>(nc) * bs) return;
+    const int i = static_cast<int>(g / bs);
+    const int I = cpts[i];
+    if (live(gate, I)) efin[static_cast<int64_t>(I) * bs + (g - static_cast<int64_t>(i) * bs)] = ec[g];
+}
+
+// The position of column a in the split copy's order: the columns outside u first.
+__device__ inline int split_pos(uint32_t u, int a, int nN) {
+    const uint32_t below = (1u << a) - 1u;
+    return (u >> a) & 1u ? nN + __popc(u & below) : __popc(~u & below);
+}
+
+// First split sweep (SplitCopy), one lane per output row and lane group: the F
+// rows' workgroups first (wgF), then the C rows'.  Bound by HBM: D^{-1} (8 bs^2
+// of a row's bytes) is loaded ahead of the row product where it fits registers.
+template <int BS, typename MT, typename VT, bool FACE = false>
+__global__ __launch_bounds__(kThreads) void k_split_first(SplitView<MT> S, int bs_rt, int G, int wgF,
+                                                         const VT *__restrict__ r, const VT *__restrict__ ec,
+                                                         VT *__restrict__ e1, VT *__restrict__ e2,
+                                                         const int *__restrict__ cpts, int nc, VT *__restrict__ efin,
+                                                         Gate gate) {
+    __shared__ double part[kThreads];
+    __shared__ double tb[kThreads];
+    const int bs = Bs<BS>::get(bs_rt);
+    if (static_cast<int>(blockIdx.x) >= wgF) {
+        split_c_rows(static_cast<int64_t>(blockIdx.x - wgF) * kThreads + threadIdx.x, ec, cpts, nc, bs, efin, gate);
+        return;
+    }
+    const Lane L = lane_of(G, bs);
+    const int f = blockIdx.x * (kThreads / (G * bs)) + L.lr;
+    int I = -1;
+    if (L.valid && f < S.nF) I = S.flist[f];
+    if (I >= 0 && !live(gate, I)) I = -1;
+    DinvRow<BS, true, FACE> dr;   // (column k of the copy's order at k bs + a)
+    const double *D = S.dinv + static_cast<int64_t>(f) * bs * bs;
+    const int64_t o = static_cast<int64_t>(I) * bs + L.a;
+    double rv = 0.0;
+    uint32_t u = 0u;
+    if (I >= 0 && L.g == 0) {
+        rv = static_cast<double>(r[o]);
+        u = S.umask[f];
+        dr.load(D, L.a);
+    }
+    double sC = 0.0, sF = 0.0;
+    if (I >= 0) {
+        const int c0 = S.rowptr[f], c1 = S.rowptr[f + 1], f0 = S.rowptr[S.nF + f], f1 = S.rowptr[S.nF + f + 1];
+        if constexpr (FACE) {
+            const FaceView<MT> F{S.meta, S.vals, nullptr, S.cmax, S.rc};
+            sC = row_part_face<BS, MT, VT, false, false, true, true>(S.ccol, F, c0, c1, L.g, G, L.a, -1, bs, ec);
+            sF = row_part_face<BS, MT, VT, false, false, true, true>(S.ccol, F, f0, f1, L.g, G, L.a, -1, bs, ec);
+        } else {
+            sC = row_part_rows<BS, MT, VT, true>(S.ccol, S.rows, c0, c1, L.g, G, L.a, bs, ec);
+            sF = row_part_rows<BS, MT, VT, true>(S.ccol, S.rows, f0, f1, L.g, G, L.a, bs, ec);
+        }
+    }
+    if (G > 1) {
+        sC = reduce_groups(sC, L, G, bs, part);
+        __syncthreads();   // (part is used again)
+        sF = reduce_groups(sF, L, G, bs, part);
+    }
+    const double sv = rv - sC;
+    const int nN = bs - __popc(u);
+    if (I >= 0 && L.g == 0) tb[L.lr * bs + split_pos(u, L.a, nN)] = sv - sF;
+    __syncthreads();
+    if (I < 0 || L.g != 0) return;
+    const double *t = tb + L.lr * bs;
+    double d = 0.0, w = 0.0;
+    if constexpr (BS > 0) {
+#pragma unroll
+        for (int k = 0; k < BS; ++k) {
+            if (k == nN) w = d;
+            d = __builtin_fma(DinvRow<BS, true, FACE>::kPre ? dr.d[DinvRow<BS, true, FACE>::kPre ? k : 0] : D[k * BS + L.a],
+                              t[k], d);
+        }
+    } else {
+        for (int k = 0; k < bs; ++k) {
+            if (k == nN) w = d;
+            d = __builtin_fma(D[k * bs + L.a], t[k], d);
+        }
+    }
+    if (nN == bs) w = d;
+    e1[o] = static_cast<VT>(d);
+    if (f >= S.n1) {
+        if (e2) e2[o] = static_cast<VT>(d);   // final: in both buffers
+    } else {
+        const int64_t q = static_cast<int64_t>(f) * bs + L.a;
+        S.s[q] = sv;
+        S.w[q] = w;
+    }
+}
+
+// A later split sweep, one lane per output row and lane group: rows [0, n) of
+// the list (wgF workgroups), then rows [n, ncopy), which the sweep before made
+// final, copied to the other buffer.
+template <int BS, typename MT, typename VT, bool FACE = false>
+__global__ __launch_bounds__(kThreads) void k_split_next(SplitView<MT> S, int bs_rt, int G, int wgF, int n, int ncopy,
+                                                        const VT *__restrict__ ein, VT *__restrict__ eout,
+                                                        Gate gate) {
+    __shared__ double part[kThreads];
+    __shared__ double tb[kThreads];
+    const int bs = Bs<BS>::get(bs_rt);
+    if (static_cast<int>(blockIdx.x) >= wgF) {
+        const int64_t g = static_cast<int64_t>(blockIdx.x - wgF) * kThreads + threadIdx.x + static_cast<int64_t>(n) * bs;
+        if (g >= static_cast<int64_t>(ncopy) * bs) return;
+        const int f = static_cast<int>(g / bs);
+        const int I = S.flist[f];
+        const int64_t o = static_cast<int64_t>(I) * bs + (g - static_cast<int64_t>(f) * bs);
+        if (live(gate, I)) eout[o] = ein[o];
+        return;
+    }
+    const Lane L = lane_of(G, bs);
+    const int f = blockIdx.x * (kThreads / (G * bs)) + L.lr;
+    int I = -1;
+    if (L.valid && f < n) I = S.flist[f];
+    if (I >= 0 && !live(gate, I)) I = -1;
+    const int64_t q = static_cast<int64_t>(f) * bs + L.a;
+    double sv = 0.0, d = 0.0;
+    uint32_t u = 0u;
+    if (I >= 0 && L.g == 0) {
+        u = S.umask[f];
+        sv = S.s[q];
+        d = S.w[q];
+    }
+    const int nU = __popc(u), nN = bs - nU;
+    const double *D = S.dinv + static_cast<int64_t>(f) * bs * bs + nN * bs + L.a;
+    // the first U columns of D^{-1} load during the row product (two faces of a Q4 element: 9)
+    constexpr int kPre = BS == 25 ? 9 : (BS == 16 ? 7 : (BS == 9 ? 5 : (BS == 4 ? 3 : 1)));
+    double dp[kPre];
+#pragma unroll
+    for (int k = 0; k < kPre; ++k) dp[k] = k < nU ? D[k * bs] : 0.0;
+    double sF = 0.0;
+    if (I >= 0) {
+        const int f0 = S.rowptr[S.nF + f], f1 = S.rowptr[S.nF + f + 1];
+        if constexpr (FACE)
+            sF = row_part_face<BS, MT, VT, false, false, true>(
+                S.colidx, FaceView<MT>{S.meta, S.vals, nullptr, S.cmax, S.rc}, f0, f1, L.g, G, L.a, -1, bs, ein);
+        else
+            sF = row_part_rows<BS, MT, VT>(S.colidx, S.rows, f0, f1, L.g, G, L.a, bs, ein);
+    }
+    sF = reduce_groups(sF, L, G, bs, part);
+    if ((u >> L.a) & 1u) tb[L.lr * bs + __popc(u & ((1u << L.a) - 1u))] = sv - sF;
+    __syncthreads();
+    if (I < 0 || L.g != 0) return;
+    const double *t = tb + L.lr * bs;
+#pragma unroll
+    for (int k = 0; k < kPre; ++k)
+        if (k < nU) d = __builtin_fma(dp[k], t[k], d);
+    for (int k = kPre; k < nU; ++k) d = __builtin_fma(D[k * bs], t[k], d);
+    eout[static_cast<int64_t>(I) * bs + L.a] = static_cast<VT>(d);
 }
 
 // The interpolation e = P e_c and the first F sweep in one launch (small
@@ -860,6 +1102,234 @@ __global__ __launch_bounds__(kThreads) void k_sweep_cr(SweepView<MT> S, const in
                 eout[static_cast<int64_t>(I) * bs + a] = static_cast<VT>(d0 + d1);
             }
         }
+    }
+}
+
+// The stored rows of R consecutive F rows of a split copy, one lane per stored
+// row, as k_sweep_cr takes them: both parts of the rows (FIRST) or the F-F part
+// alone.  A workgroup's blocks are numbered part after part, its stored rows
+// likewise (block b's first row first(b)); per pass of up to kCrCap rows each
+// block writes its column against its rows, each lane forms one row's product
+// with x, and output slot j of a thread, scalar row a of F row il, adds those of
+// its row's blocks that store row a, in block order: to sC the blocks outside F,
+// to sF the others.
+constexpr int kCrRows = 2 * kThreads / 8 + 1;
+struct SplitLds {
+    double dot[kCrCap];
+    int qcol[kCrCap];
+    uint32_t bmask[kCrBlk];
+    int bq[kCrBlk + 1];
+    int rowb[2][kCrRows];
+};
+
+template <int BS, bool FIRST, typename MT, typename VT>
+__device__ inline void split_products(SplitLds &lds, const SplitView<MT> &S, int bs, int f0, int f1,
+                                      const int *__restrict__ cols, const VT *__restrict__ x, double (&sC)[2],
+                                      double (&sF)[2]) {
+    const RowBlockView<MT> &RB = S.rows;
+    const int tf0 = S.rowptr[S.nF + f0], tf1 = S.rowptr[S.nF + f1];
+    const int tc0 = FIRST ? S.rowptr[f0] : 0, nbc = FIRST ? S.rowptr[f1] - tc0 : 0;
+    const int nbt = nbc + tf1 - tf0;
+    const int qc0 = FIRST ? RB.off[tc0] / bs : 0, nqc = FIRST ? RB.off[tc0 + nbc] / bs - qc0 : 0;
+    const int qf0 = RB.off[tf0] / bs - nqc;   // stored row v of the workgroup: qc0 + v, or qf0 + v from nqc on
+    auto block = [&](int b) { return b < nbc ? tc0 + b : tf0 + (b - nbc); };
+    auto first_g = [&](int b) { return b < nbc ? RB.off[tc0 + b] / bs - qc0 : RB.off[tf0 + (b - nbc)] / bs - qf0; };
+    const bool staged = nbt <= kCrBlk;
+    for (int k = threadIdx.x; k <= f1 - f0; k += kThreads) {
+        lds.rowb[0][k] = FIRST ? S.rowptr[f0 + k] - tc0 : 0;
+        lds.rowb[1][k] = nbc + S.rowptr[S.nF + f0 + k] - tf0;
+    }
+    if (staged)
+        for (int b = threadIdx.x; b <= nbt; b += kThreads) {
+            lds.bq[b] = first_g(b);
+            if (b < nbt) lds.bmask[b] = RB.mask[block(b)];
+        }
+    __syncthreads();
+    auto first = [&](int b) { return staged ? lds.bq[b] : first_g(b); };
+    const int nq = first(nbt);
+    const int nout = (f1 - f0) * bs;
+    for (int v0 = 0; v0 < nq; v0 += kCrCap) {
+        const int v1 = min(nq, v0 + kCrCap);
+        for (int b = threadIdx.x; b < nbt; b += kThreads) {
+            const int lo = max(first(b), v0), hi = min(first(b + 1), v1);
+            if (lo < hi) {
+                const int J = cols[block(b)];
+                for (int v = lo; v < hi; ++v) lds.qcol[v - v0] = J;
+            }
+        }
+        __syncthreads();
+        for (int v = v0 + static_cast<int>(threadIdx.x); v < v1; v += kThreads) {
+            const int J = lds.qcol[v - v0];
+            const int64_t q = v < nqc ? qc0 + v : qf0 + v;
+            // (the first sweep's coarse columns: negative where P has no row)
+            lds.dot[v - v0] = !FIRST || J >= 0
+                                  ? block_row_dot<BS>(RB.vals + q * bs, x + static_cast<int64_t>(J) * bs, bs)
+                                  : 0.0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int k = static_cast<int>(threadIdx.x) + j * kThreads;
+            if (k < nout) {
+                const int il = k / bs, a = k - il * bs;
+                const uint32_t below = (1u << a) - 1u;
+                auto add = [&](int lo, int hi, double &sum) {
+                    for (int b = lo; b < hi; ++b) {
+                        const uint32_t m = staged ? lds.bmask[b] : RB.mask[block(b)];
+                        if (!((m >> a) & 1u)) continue;
+                        const int v = first(b) + __popc(m & below);
+                        if (v >= v0 && v < v1) sum += lds.dot[v - v0];
+                    }
+                };
+                if constexpr (FIRST) add(lds.rowb[0][il], lds.rowb[0][il + 1], sC[j]);
+                add(lds.rowb[1][il], lds.rowb[1][il + 1], sF[j]);
+            }
+        }
+        if (v1 < nq) __syncthreads();   // the next pass rewrites the LDS rows
+    }
+}
+
+// First split sweep from a copy by nonzero rows, one lane per stored row (bs >=
+// 8): R F rows per workgroup (wgF of them), then the C rows' workgroups.
+template <int BS, typename MT, typename VT>
+__global__ __launch_bounds__(kThreads) void k_split_first_cr(SplitView<MT> S, int bs_rt, int R, int wgF,
+                                                            const VT *__restrict__ r, const VT *__restrict__ ec,
+                                                            VT *__restrict__ e1, VT *__restrict__ e2,
+                                                            const int *__restrict__ cpts, int nc,
+                                                            VT *__restrict__ efin, Gate gate) {
+    __shared__ SplitLds lds;
+    __shared__ double tb[2 * kThreads];
+    const int bs = Bs<BS>::get(bs_rt);
+    if (static_cast<int>(blockIdx.x) >= wgF) {
+        split_c_rows(static_cast<int64_t>(blockIdx.x - wgF) * kThreads + threadIdx.x, ec, cpts, nc, bs, efin, gate);
+        return;
+    }
+    const int f0 = blockIdx.x * R;
+    const int f1 = min(S.nF, f0 + R);
+    // a workgroup whose rows all belong to stopped systems does nothing
+    if (gate.active &&
+        !__syncthreads_or(static_cast<int>(threadIdx.x) < f1 - f0 && live(gate, S.flist[f0 + threadIdx.x])))
+        return;
+    const int nout = (f1 - f0) * bs;   // <= 2 kThreads (host)
+    // r_I and U_I load while the products run
+    double rv[2] = {0.0, 0.0};
+    uint32_t u[2] = {0u, 0u};
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int k = static_cast<int>(threadIdx.x) + j * kThreads;
+        if (k < nout) {
+            const int f = f0 + k / bs;
+            rv[j] = static_cast<double>(r[static_cast<int64_t>(S.flist[f]) * bs + (k - (k / bs) * bs)]);
+            u[j] = S.umask[f];
+        }
+    }
+    double sC[2] = {0.0, 0.0}, sF[2] = {0.0, 0.0};
+    split_products<BS, true>(lds, S, bs, f0, f1, S.ccol, ec, sC, sF);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int k = static_cast<int>(threadIdx.x) + j * kThreads;
+        rv[j] -= sC[j];   // s_I
+        if (k < nout) {
+            const int fl = k / bs, a = k - fl * bs;
+            tb[fl * bs + split_pos(u[j], a, bs - __popc(u[j]))] = rv[j] - sF[j];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int k = static_cast<int>(threadIdx.x) + j * kThreads;
+        if (k >= nout) continue;
+        const int fl = k / bs, a = k - fl * bs, f = f0 + fl;
+        const int I = S.flist[f];
+        if (!live(gate, I)) continue;
+        const double *D = S.dinv + static_cast<int64_t>(f) * bs * bs + a;
+        const double *t = tb + fl * bs;
+        const int nN = bs - __popc(u[j]);
+        double d = 0.0, w = 0.0;
+        if constexpr (BS > 0) {
+#pragma unroll
+            for (int c = 0; c < BS; ++c) {
+                if (c == nN) w = d;
+                d = __builtin_fma(D[c * BS], t[c], d);
+            }
+        } else {
+            for (int c = 0; c < bs; ++c) {
+                if (c == nN) w = d;
+                d = __builtin_fma(D[c * bs], t[c], d);
+            }
+        }
+        if (nN == bs) w = d;
+        const int64_t o = static_cast<int64_t>(I) * bs + a;
+        e1[o] = static_cast<VT>(d);
+        if (f >= S.n1) {
+            if (e2) e2[o] = static_cast<VT>(d);   // final: in both buffers
+        } else {
+            const int64_t q = static_cast<int64_t>(f) * bs + a;
+            S.s[q] = rv[j];
+            S.w[q] = w;
+        }
+    }
+}
+
+// A later split sweep from a copy by nonzero rows, one lane per stored row of
+// the F-F blocks: rows [0, n) of the list, then rows [n, ncopy) copied.
+template <int BS, typename MT, typename VT>
+__global__ __launch_bounds__(kThreads) void k_split_next_cr(SplitView<MT> S, int bs_rt, int R, int wgF, int n,
+                                                           int ncopy, const VT *__restrict__ ein,
+                                                           VT *__restrict__ eout, Gate gate) {
+    __shared__ SplitLds lds;
+    __shared__ double tb[2 * kThreads];
+    const int bs = Bs<BS>::get(bs_rt);
+    if (static_cast<int>(blockIdx.x) >= wgF) {
+        const int64_t g = static_cast<int64_t>(blockIdx.x - wgF) * kThreads + threadIdx.x + static_cast<int64_t>(n) * bs;
+        if (g >= static_cast<int64_t>(ncopy) * bs) return;
+        const int f = static_cast<int>(g / bs);
+        const int I = S.flist[f];
+        const int64_t o = static_cast<int64_t>(I) * bs + (g - static_cast<int64_t>(f) * bs);
+        if (live(gate, I)) eout[o] = ein[o];
+        return;
+    }
+    const int f0 = blockIdx.x * R;
+    const int f1 = min(n, f0 + R);
+    if (gate.active &&
+        !__syncthreads_or(static_cast<int>(threadIdx.x) < f1 - f0 && live(gate, S.flist[f0 + threadIdx.x])))
+        return;
+    const int nout = (f1 - f0) * bs;   // <= 2 kThreads (host)
+    double sv[2] = {0.0, 0.0}, d[2] = {0.0, 0.0};
+    uint32_t u[2] = {0u, 0u};
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int k = static_cast<int>(threadIdx.x) + j * kThreads;
+        if (k < nout) {
+            const int64_t q = static_cast<int64_t>(f0) * bs + k;
+            sv[j] = S.s[q];
+            d[j] = S.w[q];
+            u[j] = S.umask[f0 + k / bs];
+        }
+    }
+    double sC[2] = {0.0, 0.0}, sF[2] = {0.0, 0.0};
+    split_products<BS, false>(lds, S, bs, f0, f1, S.colidx, ein, sC, sF);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int k = static_cast<int>(threadIdx.x) + j * kThreads;
+        const int fl = k / bs, a = k - fl * bs;
+        if (k < nout && ((u[j] >> a) & 1u)) tb[fl * bs + __popc(u[j] & ((1u << a) - 1u))] = sv[j] - sF[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int k = static_cast<int>(threadIdx.x) + j * kThreads;
+        if (k >= nout) continue;
+        const int fl = k / bs, a = k - fl * bs, f = f0 + fl;
+        const int I = S.flist[f];
+        if (!live(gate, I)) continue;
+        const int nU = __popc(u[j]);
+        const double *D = S.dinv + static_cast<int64_t>(f) * bs * bs + (bs - nU) * bs + a;
+        const double *t = tb + fl * bs;
+        double v = d[j];
+#pragma unroll 5
+        for (int c = 0; c < nU; ++c) v = __builtin_fma(D[c * bs], t[c], v);
+        eout[static_cast<int64_t>(I) * bs + a] = static_cast<VT>(v);
     }
 }
 
@@ -1259,12 +1729,25 @@ void launch_residual(const MatView<MT> &A, const VT *b, const VT *x, VT *r, floa
 
 template <typename MT, typename VT>
 void launch_relax(const MatView<MT> &A, const double *dinv, bool dinv_trans, const VT *r, const VT *ein, VT *eout,
-                  const int *list, int nlist, const int8_t *cf, int only_cf, hipStream_t s, Gate gate) {
+                  const int *list, int nlist, const int8_t *cf, int only_cf, hipStream_t s, Gate gate, bool split) {
     need(A, "launch_relax");
     const int N = list ? nlist : A.nb;
     if (N <= 0) return;
     const int G = groups_for(A);
     const unsigned grid = grid_rows(N, G, A.bs);
+    if (split) {
+        if (!list || dinv_trans) fail(NAIR_EDEVICE, "launch_relax: a split sweep is a forward sweep over a list");
+        if (A.face.meta)
+            NAIR_FACE_DISPATCH(A.bs, k_relax_split, <<<grid, kThreads, 0, s>>>(A.rowptr, A.colidx, A.vals, dinv, A.bs, G,
+                                                                               r, ein, eout, list, nlist, cf, gate,
+                                                                               A.face))
+        else
+            NAIR_BS_DISPATCH(A.bs, k_relax_split, <<<grid, kThreads, 0, s>>>(A.rowptr, A.colidx, A.vals, dinv, A.bs, G,
+                                                                             r, ein, eout, list, nlist, cf, gate,
+                                                                             A.face))
+        NAIR_HIP(hipGetLastError());
+        return;
+    }
     if (list && A.sweep.rowptr) {   // F sweep from the level's sweep copy (built for this F list)
         const SweepView<MT> &S = A.sweep;
         if ((S.meta ? !S.vals : (!S.rows.mask || !S.rows.off || !S.rows.vals)) || !S.dinv || A.bs > 32)
@@ -1315,6 +1798,79 @@ void launch_relax(const MatView<MT> &A, const double *dinv, bool dinv_trans, con
     }
     NAIR_HIP(hipGetLastError());
 }
+
+// Lane groups of the split sweeps over a level's rows: as for the level's operator.
+template <typename MT>
+int split_groups(const SplitView<MT> &S, int bs, int64_t nnzb, int nb, int groups) {
+    MatView<MT> v;
+    v.nb = nb;
+    v.bs = bs;
+    v.nnzb = nnzb;
+    v.groups = groups;
+    return groups_for(v);
+}
+template <typename MT>
+void need_split(const SplitView<MT> &S, int bs, const char *what) {
+    if (bs > 32 || !S.flist || !S.rowptr || !S.colidx || !S.ccol || !S.umask || !S.dinv ||
+        (S.n1 > 0 && (!S.s || !S.w)) || (S.meta ? !S.vals : (!S.rows.mask || !S.rows.off || !S.rows.vals)))
+        fail(NAIR_EDEVICE, std::string(what) + ": incomplete split copy");
+}
+// one lane per stored row where a block has rows enough to share a wave and the blocks are kept by them
+template <typename MT>
+bool split_cr(const SplitView<MT> &S, int bs) { return !S.meta && bs >= 8; }
+#define NAIR_SPLIT_CR(KERNEL, ...)                                                          \
+    switch (bs) {                                                                           \
+        case 9: KERNEL<9, MT, VT><<<grid, kThreads, 0, s>>>(__VA_ARGS__); break;            \
+        case 16: KERNEL<16, MT, VT><<<grid, kThreads, 0, s>>>(__VA_ARGS__); break;          \
+        case 25: KERNEL<25, MT, VT><<<grid, kThreads, 0, s>>>(__VA_ARGS__); break;          \
+        default: KERNEL<0, MT, VT><<<grid, kThreads, 0, s>>>(__VA_ARGS__); break;           \
+    }
+
+template <typename MT, typename VT>
+void launch_split_first(const SplitView<MT> &S, int bs, int64_t nnzb, int nb, int groups, const VT *r, const VT *ec,
+                        VT *e1, VT *e2, const int *cpts, int nc, VT *efin, hipStream_t s, Gate gate) {
+    need_split(S, bs, "launch_split_first");
+    const int G = split_groups(S, bs, nnzb, nb, groups);
+    const unsigned wgC = nc > 0 ? grid_for(static_cast<int64_t>(nc) * bs, kThreads) : 0u;
+    if (split_cr(S, bs)) {
+        const int R = std::max(1, 2 * kThreads / (G * bs));
+        const unsigned wgF = grid_for(S.nF, R), grid = wgF + wgC;
+        NAIR_SPLIT_CR(k_split_first_cr, S, bs, R, static_cast<int>(wgF), r, ec, e1, e2, cpts, nc, efin, gate)
+    } else {
+        const unsigned wgF = grid_rows(S.nF, G, bs), grid = wgF + wgC;
+        if (S.meta)
+            NAIR_FACE_DISPATCH(bs, k_split_first, <<<grid, kThreads, 0, s>>>(S, bs, G, static_cast<int>(wgF), r, ec, e1,
+                                                                             e2, cpts, nc, efin, gate))
+        else
+            NAIR_BS_DISPATCH(bs, k_split_first, <<<grid, kThreads, 0, s>>>(S, bs, G, static_cast<int>(wgF), r, ec, e1,
+                                                                           e2, cpts, nc, efin, gate))
+    }
+    NAIR_HIP(hipGetLastError());
+}
+
+template <typename MT, typename VT>
+void launch_split_next(const SplitView<MT> &S, int bs, int64_t nnzb, int nb, int groups, int n, int ncopy,
+                       const VT *ein, VT *eout, hipStream_t s, Gate gate) {
+    need_split(S, bs, "launch_split_next");
+    if (n <= 0 || n > S.n1 || ncopy > S.nF) fail(NAIR_EDEVICE, "launch_split_next: rows outside the list");
+    const int G = split_groups(S, bs, nnzb, nb, groups);
+    const unsigned wgC = ncopy > n ? grid_for(static_cast<int64_t>(ncopy - n) * bs, kThreads) : 0u;
+    if (split_cr(S, bs)) {
+        const int R = std::max(1, 2 * kThreads / (G * bs));
+        const unsigned wgF = grid_for(n, R), grid = wgF + wgC;
+        NAIR_SPLIT_CR(k_split_next_cr, S, bs, R, static_cast<int>(wgF), n, ncopy, ein, eout, gate)
+    } else {
+        const unsigned wgF = grid_rows(n, G, bs), grid = wgF + wgC;
+        if (S.meta)
+            NAIR_FACE_DISPATCH(bs, k_split_next, <<<grid, kThreads, 0, s>>>(S, bs, G, static_cast<int>(wgF), n, ncopy,
+                                                                            ein, eout, gate))
+        else
+            NAIR_BS_DISPATCH(bs, k_split_next, <<<grid, kThreads, 0, s>>>(S, bs, G, static_cast<int>(wgF), n, ncopy,
+                                                                          ein, eout, gate))
+    }
+    NAIR_HIP(hipGetLastError());
+}
+#undef NAIR_SPLIT_CR
 
 template <typename VT>
 void launch_relax_T_first(const double *dinv, const VT *r, const int8_t *cf, VT *e0, VT *e1, int nb, int bs,
@@ -1538,7 +2094,11 @@ void launch_to_float(const double *in, float *out, int64_t n, hipStream_t s, con
     template void launch_residual<MT, VT>(const MatView<MT> &, const VT *, const VT *, VT *, float *, hipStream_t,  \
                                           Gate);                                                                     \
     template void launch_relax<MT, VT>(const MatView<MT> &, const double *, bool, const VT *, const VT *, VT *,      \
-                                       const int *, int, const int8_t *, int, hipStream_t, Gate);                    \
+                                       const int *, int, const int8_t *, int, hipStream_t, Gate, bool);              \
+    template void launch_split_first<MT, VT>(const SplitView<MT> &, int, int64_t, int, int, const VT *, const VT *,  \
+                                             VT *, VT *, const int *, int, VT *, hipStream_t, Gate);                 \
+    template void launch_split_next<MT, VT>(const SplitView<MT> &, int, int64_t, int, int, int, int, const VT *,     \
+                                            VT *, hipStream_t, Gate);                                                \
     template void launch_restrict<MT, VT>(const MatView<MT> &, const VT *, const int *, VT *, hipStream_t, Gate);    \
     template void launch_interp<VT>(const int *, const VT *, VT *, VT *, int, int, hipStream_t, Gate);               \
     template void launch_relax_interp<MT, VT>(const MatView<MT> &, const double *, const VT *, const int *,          \

@@ -68,7 +68,9 @@ struct Level {
     // face-compressed copies of A and A^T (level 0 of a block hierarchy)
     FaceCopy face, faceT;
     // F rows of A and A^T in F-list order without their diagonal blocks, for the sweeps
+    // (A's on the levels of at least kFewLanes lanes: as a split copy)
     SweepCopy sweep, sweepT;
+    SplitCopy split;
     // Z's blocks by their nonzero rows, for the restriction (levels with sweep copies)
     RowBlocks zrows;
     // bit masks of the nonzero rows of Z's and A's blocks, where the kernels
@@ -100,6 +102,21 @@ inline MatView<float> op_view32(const Level &L, bool trans) {
                                    S.dinv.get(), S.cmax, S.rc,
                                    RowBlockView<float>{S.rows.mask.get(), S.rows.off.get(), S.rows.vals32.get()}};
     return v;
+}
+
+inline SplitView<double> split_view(const Level &L) {
+    const SplitCopy &S = L.split;
+    return SplitView<double>{L.flist.get(), S.nF, S.n1, S.rowptr.get(), S.colidx.get(), S.ccol.get(),
+                             S.rc ? S.meta.get() : nullptr, S.vals.get(), S.cmax, S.rc,
+                             RowBlockView<double>{S.rows.mask.get(), S.rows.off.get(), S.rows.vals.get()},
+                             S.umask.get(), S.dinv.get(), S.s.get(), S.w.get()};
+}
+inline SplitView<float> split_view32(const Level &L) {
+    const SplitCopy &S = L.split;
+    return SplitView<float>{L.flist.get(), S.nF, S.n1, S.rowptr.get(), S.colidx.get(), S.ccol.get(),
+                            S.rc ? S.meta.get() : nullptr, S.vals32.get(), S.cmax, S.rc,
+                            RowBlockView<float>{S.rows.mask.get(), S.rows.off.get(), S.rows.vals32.get()},
+                            S.umask.get(), S.dinv.get(), S.s.get(), S.w.get()};
 }
 
 inline TransRowsView<double> tr_view(const TransRows &T, int bs) {

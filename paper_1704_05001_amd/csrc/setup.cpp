@@ -478,6 +478,25 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
 
 void build_sweeps(Hier &h, bool trans, hipStream_t s) {
     if (h.prm.sweep_copy == 0) return;
+    // the large levels' forward sweeps read split copies: their F lists in order of depth first
+    if (!trans) {
+        std::vector<Level *> lv;
+        for (auto &Lp : h.lv)
+            if (!Lp->coarsest && Lp->nF > 0 && Lp->nF <= INT_MAX / 3 && !few_lanes(Lp->A.nb, Lp->A.bs))
+                lv.push_back(Lp.get());
+        if (!lv.empty()) {
+            DBuf<int> counts(2 * lv.size());
+            for (size_t k = 0; k < lv.size(); ++k)
+                order_by_depth(lv[k]->A, lv[k]->cf.get(), lv[k]->flist, lv[k]->nF, counts.get() + 2 * k, s);
+            std::vector<int> hc(2 * lv.size());
+            read_ints(counts.get(), hc.data(), static_cast<int>(hc.size()), s);
+            for (size_t k = 0; k < lv.size(); ++k) {
+                Level &L = *lv[k];
+                build_split(L.A, L.face, L.dinv.get(), L.cf.get(), L.pmap.get(), L.flist.get(), L.nF, hc[2 * k + 1],
+                            hc[2 * k], L.split, s, L.amask.get());
+            }
+        }
+    }
     for (auto &Lp : h.lv) {
         Level &L = *Lp;
         if (L.coarsest || L.nF <= 0) continue;
@@ -485,7 +504,7 @@ void build_sweeps(Hier &h, bool trans, hipStream_t s) {
         if (trans && (L.atF.on || !L.AT.rowptr.get())) continue;   // the transposed sweeps read A's rows
         SweepCopy &S = trans ? L.sweepT : L.sweep;
         // (A's row masks, where the Galerkin step gave them, are no use for A^T)
-        if (!S.on)
+        if (!S.on && (trans || few_lanes(L.A.nb, L.A.bs)))
             build_sweep(trans ? L.AT : L.A, trans ? L.faceT : L.face, L.dinv.get(), L.flist.get(), L.nF, S, s, trans,
                         trans ? nullptr : L.amask.get());
         if (!trans && !L.zrows.on && L.Z.nnzb > 0)
@@ -529,6 +548,7 @@ void make_fp32_copies(Hier &h, hipStream_t s) {
         trans_rows_to_float(L.atF, L.A.bs, s);
         trans_rows_to_float(L.zt, L.A.bs, s);
         sweep_to_float(L.sweep, L.A.bs, s);
+        split_to_float(L.split, L.A.bs, s);
         sweep_to_float(L.sweepT, L.A.bs, s);
         row_blocks_to_float(L.zrows, L.Z.nnzb, L.A.bs, s);
     }

@@ -24,6 +24,7 @@ struct Store;
 template <>
 struct Store<double> {
     static MatView<double> A(const Level &L) { return op_view(L, false).with_groups(L.tune[TU_RELAX]); }
+    static SplitView<double> split(const Level &L) { return split_view(L); }
     static MatView<double> Z(const Level &L) { return z_view(L).with_groups(L.tune[TU_RESTRICT]); }
     static MatView<double> AT(const Level &L) { return op_view(L, true).with_groups(L.tune[TU_RELAX_T]); }
     static MatView<double> ZT(const Level &L) { return view(L.ZT).with_groups(L.tune[TU_INTERP_T]); }
@@ -42,6 +43,7 @@ struct Store<double> {
 template <>
 struct Store<float> {
     static MatView<float> A(const Level &L) { return op_view32(L, false).with_groups(L.tune[TU_RELAX]); }
+    static SplitView<float> split(const Level &L) { return split_view32(L); }
     static MatView<float> Z(const Level &L) { return z_view32(L).with_groups(L.tune[TU_RESTRICT]); }
     static MatView<float> AT(const Level &L) { return op_view32(L, true).with_groups(L.tune[TU_RELAX_T]); }
     static MatView<float> ZT(const Level &L) { return view(L.ZT, L.zt32.get()).with_groups(L.tune[TU_INTERP_T]); }
@@ -95,15 +97,33 @@ const T *cycle(Hier &h, int l, bool fcyc, hipStream_t s) {
         launch_restrict<T, T>(S::Z(L), S::r(L), L.cpts.get(), S::r(C), s, gate(h, C));
     }
     const T *ec = coarse_solve<T>(h, l + 1, fcyc, s);
-    // on a small level the interpolation rides along with the first sweep
-    const bool fuse = few_lanes(L.A.nb, bs) && !L.face.on;
-    if (!fuse) {
-        TimerScope ts(TK_INTERP, l, s);
-        launch_interp<T>(L.pmap.get(), ec, S::e0(L), S::e1(L), L.A.nb, bs, s, gate(h, L));
-    }
+    const bool small = few_lanes(L.A.nb, bs);
     const MatView<T> A = S::A(L);
     T *cur = S::e0(L), *oth = S::e1(L);
-    {
+    if (L.split.on) {   // interpolation and sweeps from the split copy (see SplitCopy)
+        const SplitView<T> P = S::split(L);
+        const int n1 = L.split.n1, n2 = L.split.n2;
+        // sweeps that still change a row: no more than the depth of the F-F couplings
+        const int nu = n1 == 0 ? 1 : (n2 == 0 ? std::min(2, h.prm.degree + 1) : h.prm.degree + 1);
+        T *e1 = oth, *e2 = cur;   // sweep m writes e1 (m odd) or e2 (m even)
+        const int G = L.tune[TU_RELAX];
+        TimerScope ts(TK_RELAX, l, s, h.prm.degree + 1);
+        launch_split_first<T, T>(P, bs, L.A.nnzb, L.A.nb, G, S::r(L), ec, e1, nu > 1 ? e2 : nullptr, L.cpts.get(),
+                                 L.nc, nu % 2 == 1 ? e1 : e2, s, gate(h, L));
+        for (int m = 2; m <= nu; ++m) {
+            const int n = m == 2 ? n1 : n2;   // rows that change; those the sweep before made final are copied
+            launch_split_next<T, T>(P, bs, L.A.nnzb, L.A.nb, G, n, m == 3 ? n1 : n, m % 2 == 0 ? e1 : e2,
+                                    m % 2 == 0 ? e2 : e1, s, gate(h, L));
+        }
+        cur = nu % 2 == 1 ? e1 : e2;
+        oth = nu % 2 == 1 ? e2 : e1;
+    } else {
+        // on a small level the interpolation rides along with the first sweep
+        const bool fuse = small && !L.face.on;
+        if (!fuse) {
+            TimerScope ts(TK_INTERP, l, s);
+            launch_interp<T>(L.pmap.get(), ec, S::e0(L), S::e1(L), L.A.nb, bs, s, gate(h, L));
+        }
         // the nu sweeps run back to back; one event pair brackets the group
         TimerScope ts(TK_RELAX, l, s, h.prm.degree + 1);
         int k = 0;
@@ -115,7 +135,7 @@ const T *cycle(Hier &h, int l, bool fcyc, hipStream_t s) {
         }
         for (; k <= h.prm.degree; ++k) {
             launch_relax<T, T>(A, L.dinv.get(), false, S::r(L), cur, oth, L.flist.get(), L.nF, L.cf.get(), 0, s,
-                               gate(h, L));
+                               gate(h, L), !small);
             std::swap(cur, oth);
         }
     }

@@ -145,7 +145,219 @@ __global__ __launch_bounds__(256) void k_rb_fill(const double *__restrict__ vals
     }
 }
 
+// Depth class of F row f (I = flist[f]) as a flag in one of three lists one
+// after another (class 2, 1, 0): whether row I has an F-F block, and whether one
+// of those F neighbours has one itself.  Index work only: the pattern rows of I
+// and of its F neighbours.
+__global__ __launch_bounds__(256) void k_depth_class(const int *__restrict__ rowptr, const int *__restrict__ colidx,
+                                                    const int8_t *__restrict__ cf, const int *__restrict__ flist,
+                                                    int nF, int *__restrict__ flag) {
+    const int f = blockIdx.x * blockDim.x + threadIdx.x;
+    if (f >= nF) return;
+    const int I = flist[f];
+    int d = 0;
+    for (int t = rowptr[I]; t < rowptr[I + 1] && d < 2; ++t) {
+        const int J = colidx[t];
+        if (J == I || cf[J] != 0) continue;
+        d = 1;
+        for (int q = rowptr[J]; q < rowptr[J + 1] && d < 2; ++q) {
+            const int K = colidx[q];
+            if (K != J && cf[K] == 0) d = 2;
+        }
+    }
+    for (int c = 0; c < 3; ++c) flag[static_cast<int64_t>(c) * nF + f] = d == 2 - c ? 1 : 0;
+}
+
+__global__ __launch_bounds__(256) void k_depth_place(const int *__restrict__ flist, const int *__restrict__ flag,
+                                                    const int *__restrict__ pos, int nF, int *__restrict__ out,
+                                                    int *__restrict__ counts) {
+    const int f = blockIdx.x * blockDim.x + threadIdx.x;
+    if (f < 2) counts[f] = pos[(f + 1) * static_cast<int64_t>(nF)];
+    if (f >= nF) return;
+    for (int c = 0; c < 3; ++c) {
+        const int64_t k = static_cast<int64_t>(c) * nF + f;
+        if (flag[k]) out[pos[k]] = flist[f];
+    }
+}
+
+// Blocks of F row f in columns outside F -> cnt[f], in F columns other than its own -> cnt[nF + f].
+__global__ __launch_bounds__(256) void k_split_count(const int *__restrict__ rowptr, const int *__restrict__ colidx,
+                                                    const int8_t *__restrict__ cf, const int *__restrict__ flist,
+                                                    int nF, int *__restrict__ cnt) {
+    const int f = blockIdx.x * blockDim.x + threadIdx.x;
+    if (f >= nF) return;
+    const int I = flist[f];
+    int c = 0, e = 0;
+    for (int t = rowptr[I]; t < rowptr[I + 1]; ++t) {
+        const int J = colidx[t];
+        if (J == I) continue;
+        if (cf[J] == 0) ++e;
+        else ++c;
+    }
+    cnt[f] = c;
+    cnt[nF + f] = e;
+}
+
+// One wave per F row: its blocks' columns, coarse columns and source block
+// indices (with FACE also the face masks) to their places, both parts in order.
+template <bool FACE>
+__global__ __launch_bounds__(256) void k_split_fill(const int *__restrict__ rowptr, const int *__restrict__ colidx,
+                                                   const int8_t *__restrict__ cf, const int *__restrict__ pmap,
+                                                   const uint64_t *__restrict__ fmeta,
+                                                   const int *__restrict__ flist, int nF, int64_t cap,
+                                                   const int *__restrict__ orp, int *__restrict__ ocol,
+                                                   int *__restrict__ occol, uint64_t *__restrict__ ometa,
+                                                   int *__restrict__ osrc) {
+    const int lane = threadIdx.x & 63;
+    const int f = blockIdx.x * 4 + static_cast<int>(threadIdx.x >> 6);
+    if (f >= nF) return;   // whole waves
+    const int I = flist[f];
+    const int lo = rowptr[I], hi = rowptr[I + 1];
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int64_t oc = orp[f], of = orp[nF + f];
+    for (int base = lo; base < hi; base += 64) {
+        const int t = base + lane;
+        const int J = t < hi ? colidx[t] : I;
+        const bool keep = J != I;
+        const bool inF = keep && cf[J] == 0;
+        const unsigned long long bf = __ballot(inF), bc = __ballot(keep && !inF);
+        const int64_t d = inF ? of + __popcll(bf & below) : oc + __popcll(bc & below);
+        if (keep && d < cap) {
+            ocol[d] = J;
+            occol[d] = pmap[J];
+            osrc[d] = t;
+            if constexpr (FACE) ometa[d] = fmeta[t];
+        }
+        of += __popcll(bf);
+        oc += __popcll(bc);
+    }
+}
+
+// out's w-word rectangle d = vals' rectangle src[d], d < *count: one thread per word
+__global__ __launch_bounds__(256) void k_take_rects(const double *__restrict__ vals, const int *__restrict__ src,
+                                                   const int *__restrict__ count, int64_t cap, int w,
+                                                   double *__restrict__ out) {
+    const int64_t g = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t d = g / w;
+    if (d >= cap || d >= *count) return;
+    out[g] = vals[static_cast<int64_t>(src[d]) * w + (g - d * w)];
+}
+
+// One wave per F row: U_I, the union of its F-F blocks' nonzero rows (low words
+// of the face masks, or row masks), and D_I^{-1} column by column, the columns
+// outside U_I first (coefficient of the k-th such column for output a at k bs + a).
+__global__ __launch_bounds__(256) void k_split_dinv(const double *__restrict__ dinv, const int *__restrict__ flist,
+                                                   int nF, int bs, const int *__restrict__ orp,
+                                                   const uint64_t *__restrict__ meta,
+                                                   const uint32_t *__restrict__ rmask, uint32_t *__restrict__ umask,
+                                                   double *__restrict__ odinv) {
+    __shared__ int cols[4][32];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int f = blockIdx.x * 4 + wv;
+    if (f >= nF) return;   // whole waves
+    uint32_t u = 0;
+    for (int t = orp[nF + f]; t < orp[nF + f + 1]; ++t) u |= meta ? static_cast<uint32_t>(meta[t]) : rmask[t];
+    if (lane == 0) umask[f] = u;
+    const int nN = bs - __popc(u);
+    if (lane < bs) {
+        const uint32_t below = (1u << lane) - 1u;
+        const int pos = (u >> lane) & 1u ? nN + __popc(u & below) : __popc(~u & below);
+        cols[wv][pos] = lane;
+    }
+    __builtin_amdgcn_wave_barrier();   // (each wave its own LDS row)
+    const int bb = bs * bs;
+    const double *Di = dinv + static_cast<int64_t>(flist[f]) * bb;
+    double *Do = odinv + static_cast<int64_t>(f) * bb;
+    // every load first (bs <= 32: at most 16 words per lane; words past the block repeat its last), then the stores
+    constexpr int kChunks = 16;
+    double v[kChunks];
+#pragma unroll
+    for (int i = 0; i < kChunks; ++i) {
+        const int e = lane + 64 * i < bb ? lane + 64 * i : bb - 1;
+        const int k = e / bs, a = e - k * bs;
+        v[i] = Di[a * bs + cols[wv][k]];
+    }
+#pragma unroll
+    for (int i = 0; i < kChunks; ++i) {
+        const int e = lane + 64 * i;
+        if (e < bb) Do[e] = v[i];
+    }
+}
+
 }  // namespace
+
+void order_by_depth(const DevBSR &A, const int8_t *cf, DBuf<int> &flist, int nF, int *counts, hipStream_t s) {
+    DBuf<int> flag(static_cast<size_t>(nF) * 3), pos(static_cast<size_t>(nF) * 3 + 1), out(static_cast<size_t>(nF));
+    const unsigned grid = grid_for(nF, 256);
+    k_depth_class<<<grid, 256, 0, s>>>(A.rowptr.get(), A.colidx.get(), cf, flist.get(), nF, flag.get());
+    NAIR_HIP(hipGetLastError());
+    scan_exclusive(flag.get(), pos.get(), 3 * nF, s);
+    k_depth_place<<<grid, 256, 0, s>>>(flist.get(), flag.get(), pos.get(), nF, out.get(), counts);
+    NAIR_HIP(hipGetLastError());
+    flist = std::move(out);
+}
+
+void build_split(const DevBSR &A, const FaceCopy &F, const double *dinv, const int8_t *cf, const int *pmap,
+                 const int *flist, int nF, int n1, int n2, SplitCopy &S, hipStream_t s, const uint32_t *amask) {
+    S = SplitCopy();
+    const int bs = A.bs;
+    if (nF <= 0 || bs > 32) return;
+    const bool face = F.on;
+    S.nF = nF;
+    S.n1 = n1;
+    S.n2 = n2;
+    S.rc = face ? F.rc : 0;
+    S.cmax = face ? F.cmax : 0;
+    S.cap = std::max<int64_t>(A.nnzb - nF, 1);   // (every row holds its diagonal block)
+    S.rowptr.alloc(2 * static_cast<size_t>(nF) + 1);
+    S.colidx.alloc(static_cast<size_t>(S.cap));
+    S.ccol.alloc(static_cast<size_t>(S.cap));
+    S.umask.alloc(static_cast<size_t>(nF));
+    S.dinv.alloc(static_cast<size_t>(nF) * bs * bs);
+    S.s.alloc(static_cast<size_t>(n1) * bs);
+    S.w.alloc(static_cast<size_t>(n1) * bs);
+    DBuf<int> cnt(2 * static_cast<size_t>(nF)), src(static_cast<size_t>(S.cap));
+    k_split_count<<<grid_for(nF, 256), 256, 0, s>>>(A.rowptr.get(), A.colidx.get(), cf, flist, nF, cnt.get());
+    NAIR_HIP(hipGetLastError());
+    scan_exclusive(cnt.get(), S.rowptr.get(), 2 * nF, s);
+    const int *total = S.rowptr.get() + 2 * static_cast<int64_t>(nF);
+    const unsigned grid = static_cast<unsigned>((nF + 3) / 4);
+    if (face) {
+        S.meta.alloc(static_cast<size_t>(S.cap));
+        S.vals.alloc(static_cast<size_t>(S.cap) * F.rc);
+        k_split_fill<true><<<grid, 256, 0, s>>>(A.rowptr.get(), A.colidx.get(), cf, pmap, F.meta.get(), flist, nF,
+                                                S.cap, S.rowptr.get(), S.colidx.get(), S.ccol.get(), S.meta.get(),
+                                                src.get());
+        NAIR_HIP(hipGetLastError());
+        k_take_rects<<<grid_for(S.cap * F.rc, 256), 256, 0, s>>>(F.vals.get(), src.get(), total, S.cap, F.rc,
+                                                                S.vals.get());
+        NAIR_HIP(hipGetLastError());
+    } else {
+        k_split_fill<false><<<grid, 256, 0, s>>>(A.rowptr.get(), A.colidx.get(), cf, pmap, nullptr, flist, nF, S.cap,
+                                                 S.rowptr.get(), S.colidx.get(), S.ccol.get(), nullptr, src.get());
+        NAIR_HIP(hipGetLastError());
+        if (!build_row_blocks(A.vals.get(), S.cap, bs, S.rows, s, src.get(), total, amask)) {
+            S = SplitCopy();
+            return;
+        }
+    }
+    k_split_dinv<<<grid, 256, 0, s>>>(dinv, flist, nF, bs, S.rowptr.get(), face ? S.meta.get() : nullptr,
+                                      S.rows.mask.get(), S.umask.get(), S.dinv.get());
+    NAIR_HIP(hipGetLastError());
+    S.on = true;
+}
+
+void split_to_float(SplitCopy &S, int bs, hipStream_t s) {
+    if (!S.on) return;
+    if (S.rc > 0) {
+        if (S.vals32.get()) return;
+        const int64_t nv = S.cap * S.rc;
+        S.vals32.alloc(static_cast<size_t>(nv));
+        launch_to_float(S.vals.get(), S.vals32.get(), nv, s);
+    } else {
+        row_blocks_to_float(S.rows, S.cap, bs, s);
+    }
+}
 
 bool build_row_blocks(const double *vals, int64_t n, int bs, RowBlocks &R, hipStream_t s, const int *src,
                       const int *count, const uint32_t *masks) {

@@ -63,6 +63,7 @@ struct Vecs;
 template <>
 struct Vecs<double> {
     static MatView<double> A(const Level &L) { return op_view(L, false); }
+    static SplitView<double> split(const Level &L) { return split_view(L); }
     static MatView<double> Z(const Level &L) { return z_view(L); }
     static MatView<double> AT(const Level &L) { return op_view(L, true); }
     static MatView<double> ZT(const Level &L) { return view(L.ZT); }
@@ -76,6 +77,7 @@ struct Vecs<double> {
 template <>
 struct Vecs<float> {
     static MatView<float> A(const Level &L) { return op_view32(L, false); }
+    static SplitView<float> split(const Level &L) { return split_view32(L); }
     static MatView<float> Z(const Level &L) { return z_view32(L); }
     static MatView<float> AT(const Level &L) { return op_view32(L, true); }
     static MatView<float> ZT(const Level &L) { return view(L.ZT, L.zt32.get()); }
@@ -110,8 +112,19 @@ void tune_levels(Hier &h, int reps, hipStream_t s) {
         const MatView<T> A = V::A(L), Z = V::Z(L);
         L.tune[TU_RELAX] = pick(
             [&](int G) {
-                launch_relax<T, T>(A.with_groups(G), L.dinv.get(), false, V::r(L), V::e0(L), V::e1(L),
-                                   L.flist.get(), L.nF, L.cf.get(), 0, s);
+                if (!L.split.on) {
+                    launch_relax<T, T>(A.with_groups(G), L.dinv.get(), false, V::r(L), V::e0(L), V::e1(L),
+                                       L.flist.get(), L.nF, L.cf.get(), 0, s, Gate(), true);
+                    return;
+                }
+                // the sweeps of one cycle visit
+                const SplitView<T> P = V::split(L);
+                launch_split_first<T, T>(P, bs, L.A.nnzb, L.A.nb, G, V::r(L), V::e0(C), V::e1(L), V::e0(L),
+                                         L.cpts.get(), L.nc, V::e1(L), s);
+                for (int m = 2; m <= h.prm.degree + 1; ++m) {
+                    const int n = m == 2 ? L.split.n1 : L.split.n2;
+                    if (n > 0) launch_split_next<T, T>(P, bs, L.A.nnzb, L.A.nb, G, n, n, V::e1(L), V::e0(L), s);
+                }
             },
             bs, reps, ev, s);
         // the transposed cycle's kernels: from the transposed row copies where the level has them
