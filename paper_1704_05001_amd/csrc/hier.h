@@ -200,7 +200,26 @@ struct Hier {
     BatchSolve batch;
     Krylov krylov;
     const int *active = nullptr;    // during a batched solve: per-system "still iterating" flags
+    // collapsed coarse cycle (one system): the coarse solve on level `collapse` (0: none) as a
+    // dense matrix of the level's unknowns ([0]: of a V-cycle, [1]: of an F-cycle), and the
+    // transposes once a transposed cycle needs them
+    int collapse = 0;
+    DBuf<double> coarse_op[2], coarse_opT[2];
 };
+
+// The first level below the finest of at most kCollapse unknowns in at most
+// kCollapseRows block rows takes the collapsed coarse cycle (it must not be the
+// coarsest).  Its product replaces the launches of the levels below (4 to 5 of 3
+// to 6 us per level and visit); forming it grows with the cube of the order.  At
+// Q2 97 x 97 (orders 540 or 1440 by the bound) a bound of 2048 against 1024 cost
+// 0.07 ms of setup and gained 15 us per cycle; scalar levels of 1893 rows cost
+// 0.4 ms where they gained 0.3 ms in 13 iterations, hence the bound on rows.
+constexpr int kCollapse = 2048, kCollapseRows = 1024;
+void build_collapse(Hier &h, hipStream_t s);
+void collapse_transpose(Hier &h, hipStream_t s);
+// e = (the collapsed coarse solve of a V- or F-cycle, or its transpose) r
+template <typename VT>
+void launch_collapsed(const Hier &h, bool fcyc, bool trans, const VT *r, VT *e, hipStream_t s);
 
 // nsys systems of sys_nb[s] block rows each (host array), stored one after the
 // other in one BSR matrix with no block coupling two systems.

@@ -470,6 +470,7 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
     }
     // the finest operator is read by every cycle: a compact copy of its face blocks
     if (p.faces == 1 && p.form == 0) build_face(h.lv[0]->A, h.lv[0]->face, s, &h.lv[0]->facemeta);
+    build_collapse(h, s);
     build_sweeps(h, false, s);
     if (p.precision == 1) make_fp32_copies(h, s);
     prepare_cycle(h, false, s);   // the F-cycle's saved vectors
@@ -559,8 +560,10 @@ void ensure_transposes(Hier &h, hipStream_t s) {
         bsr_transpose(h.A0, h.A0T, s);
         h.have_A0T = true;
     }
+    collapse_transpose(h, s);
     for (size_t l = 0; l < h.lv.size(); ++l) {
         Level &L = *h.lv[l];
+        if (h.collapse > 0 && static_cast<int>(l) >= h.collapse) break;   // (the cycle does not go there)
         if (L.have_T) continue;
         // below the finest level, the transposed sweeps and residual read A's
         // rows transposed by their nonzero rows (only the F rows: with F

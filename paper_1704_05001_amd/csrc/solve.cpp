@@ -203,8 +203,12 @@ const T *cycle_T(Hier &h, int l, bool fcyc, hipStream_t s) {
 // residual replaces r_l, and the V-cycle's correction is added.
 template <typename T>
 const T *coarse_solve(Hier &h, int l, bool fcyc, hipStream_t s) {
-    if (!fcyc) return cycle<T>(h, l, false, s);
     using S = Store<T>;
+    if (l == h.collapse) {   // (>= 1 where there is one)
+        launch_collapsed<T>(h, fcyc, false, S::r(*h.lv[l]), S::e0(*h.lv[l]), s);
+        return S::e0(*h.lv[l]);
+    }
+    if (!fcyc) return cycle<T>(h, l, false, s);
     Level &L = *h.lv[l];
     const Gate g = gate(h, L);
     const T *e1 = cycle<T>(h, l, true, s);
@@ -219,8 +223,12 @@ const T *coarse_solve(Hier &h, int l, bool fcyc, hipStream_t s) {
 // Its transpose: y = V^T r + F^T (r - A^T V^T r).
 template <typename T>
 const T *coarse_solve_T(Hier &h, int l, bool fcyc, hipStream_t s) {
-    if (!fcyc) return cycle_T<T>(h, l, false, s);
     using S = Store<T>;
+    if (l == h.collapse) {
+        launch_collapsed<T>(h, fcyc, true, S::r(*h.lv[l]), S::e0(*h.lv[l]), s);
+        return S::e0(*h.lv[l]);
+    }
+    if (!fcyc) return cycle_T<T>(h, l, false, s);
     Level &L = *h.lv[l];
     const Gate g = gate(h, L);
     const T *y1 = cycle_T<T>(h, l, false, s);
