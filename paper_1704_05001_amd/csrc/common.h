@@ -481,6 +481,28 @@ struct SplitView {
     double *s = nullptr, *w = nullptr;
 };
 
+// ------------------------------------------------------------ short rows
+// On a level below kFewLanes lanes a launch moves little data: the chain of
+// dependent loads (F list -> row range -> column -> vector entry) sets its time.
+// Its F rows and Z's rows keep the columns of their first kShort blocks at a
+// place that follows from the row's number, beside a header, so that a row's
+// values, vector entries and D^{-1} all load one step after the launch starts.
+// hdr[f] = {fine block row, blocks off the diagonal, first block of A's row,
+// blocks before the diagonal}; ent[f kShort + k] = {column, its coarse index
+// through the one-point map (-1: none)} of the k-th off-diagonal block, which is
+// block first + k (+ 1 past the diagonal) of A.  zhdr[i] = {fine block row of C
+// point i, blocks, first block, 0}; zent[i kShort + k] the k-th block's column.
+// Blocks past kShort are found in A's (Z's) own index arrays.
+constexpr int kShort = 16;
+struct ShortRows {
+    bool on = false;
+    DBuf<int4> hdr, zhdr;
+    DBuf<int2> ent;
+    DBuf<int> zent;
+};
+void build_short_rows(const DevBSR &A, const DevBSR &Z, const int *flist, int nF, const int *cpts, int nc,
+                      const int *pmap, ShortRows &S, hipStream_t s);
+
 template <typename MT>
 struct SweepView {
     const int *rowptr = nullptr, *colidx = nullptr;
@@ -544,6 +566,16 @@ template <typename MT, typename VT>
 void launch_relax(const MatView<MT> &A, const double *dinv, bool dinv_trans, const VT *r, const VT *ein, VT *eout,
                   const int *list, int nlist, const int8_t *cf, int only_cf, hipStream_t s, Gate g = Gate(),
                   bool split = false);
+// F sweep of a level with short rows: from e = P e_c (first: C rows of e0 and e1 take e_c, F rows of e1 the
+// sweep), or from e0 to e1's F rows
+template <typename MT, typename VT>
+void launch_short_sweep(const MatView<MT> &A, const ShortRows &S, int nF, bool first, const double *dinv, const VT *r,
+                        const VT *ec, const int *pmap, const int *cpts, int nc, VT *e0, VT *e1, hipStream_t s,
+                        Gate g = Gate());
+// r_c = r_C + Z r_F on a level with short rows (gate of the coarse rows)
+template <typename MT, typename VT>
+void launch_short_restrict(const MatView<MT> &Z, const ShortRows &S, const VT *r, VT *rc, hipStream_t s,
+                           Gate g = Gate());
 // First split sweep, from e = P e_c: e1_F (and e2_F on the rows of depth 0; e2 nullable), s and w on the
 // others, and efin_C = e_c on the nc C rows.  groups: lane groups per row (0: from the row length)
 template <typename MT, typename VT>
@@ -566,11 +598,6 @@ void launch_restrict(const MatView<MT> &Z, const VT *r, const int *cpts, VT *rc,
 template <typename VT>
 void launch_restrict_T(const int *ptptr, const int *ptidx, const VT *s, VT *sc, int nc, int bs, hipStream_t st,
                        Gate g = Gate());
-// e0 = P e_c everywhere, e1 = e0 + D^{-1}(r - A e0) on F rows (e0 on C rows):
-// the interpolation and the first F sweep in one launch
-template <typename MT, typename VT>
-void launch_relax_interp(const MatView<MT> &A, const double *dinv, const VT *r, const int *pmap, const VT *ec,
-                         const int8_t *cf, VT *e0, VT *e1, hipStream_t s, Gate gate = Gate());
 template <typename MT, typename VT>
 void launch_interp_T(const MatView<MT> &ZT, const int *cidx, const VT *yc, VT *y, hipStream_t s, Gate g = Gate());
 // The transposed cycle's products read from TransRows copies (coarse levels):

@@ -32,27 +32,6 @@ struct Bs<0> {
     __device__ static int get(int bs) { return bs; }
 };
 
-// Where a row product reads the block vector of column J.
-template <typename VT>
-struct PlainSrc {
-    const VT *x;
-    int bs;
-    static constexpr bool kMaySkip = false;
-    __device__ const VT *row(int j) const { return x + static_cast<int64_t>(j) * bs; }
-};
-// x = P e_c read through the one-point map: block J is e_c's block pmap[J], or
-// zero (skipped: its products would add zeros) when pmap[J] < 0.
-template <typename VT>
-struct PmapSrc {
-    const VT *ec;
-    const int *pmap;
-    int bs;
-    static constexpr bool kMaySkip = true;
-    __device__ const VT *row(int j) const {
-        const int p = pmap[j];
-        return p >= 0 ? ec + static_cast<int64_t>(p) * bs : nullptr;
-    }
-};
 // One block row's product with x_J: sum over c of blk[c] x_J[c], the even and
 // the odd c summed apart and then added.  Every row product below adds these
 // per-block sums in block order, whichever lanes form them, so the kernels that
@@ -78,9 +57,9 @@ __device__ inline double block_row_dot(const MT *__restrict__ blk, const VT *__r
 
 // sum over blocks t = lo+g, lo+g+G, ... < hi of (block t row a) . x[col t];
 // with SKIP, the block in column `skip` (the row's diagonal block) is left out.
-template <int BS, typename MT, typename VT, typename SRC, bool SKIP = false>
-__device__ inline double row_part_src(const int *__restrict__ colidx, const MT *__restrict__ vals, int lo, int hi,
-                                      int g, int G, int a, int bs_rt, const SRC &src, int skip = -1) {
+template <int BS, typename MT, typename VT, bool SKIP = false>
+__device__ inline double row_part(const int *__restrict__ colidx, const MT *__restrict__ vals, int lo, int hi, int g,
+                                  int G, int a, int bs_rt, const VT *__restrict__ x, int skip = -1) {
     const int bs = Bs<BS>::get(bs_rt);
     const int64_t bb = static_cast<int64_t>(bs) * bs;
     double acc = 0.0;
@@ -90,20 +69,9 @@ __device__ inline double row_part_src(const int *__restrict__ colidx, const MT *
         if constexpr (SKIP) {
             if (J == skip) continue;
         }
-        const VT *xj = src.row(J);
-        if constexpr (SRC::kMaySkip) {
-            if (xj == nullptr) continue;
-        }
-        acc += block_row_dot<BS>(blk, xj, bs);
+        acc += block_row_dot<BS>(blk, x + static_cast<int64_t>(J) * bs, bs);
     }
     return acc;
-}
-
-template <int BS, typename MT, typename VT, bool SKIP = false>
-__device__ inline double row_part(const int *__restrict__ colidx, const MT *__restrict__ vals, int lo, int hi, int g,
-                                  int G, int a, int bs_rt, const VT *__restrict__ x, int skip = -1) {
-    return row_part_src<BS, MT, VT, PlainSrc<VT>, SKIP>(colidx, vals, lo, hi, g, G, a, bs_rt,
-                                                        PlainSrc<VT>{x, Bs<BS>::get(bs_rt)}, skip);
 }
 
 // The same row product over a face-compressed copy: the diagonal block whole
@@ -827,46 +795,105 @@ __global__ __launch_bounds__(kThreads) void k_split_next(SplitView<MT> S, int bs
     eout[static_cast<int64_t>(I) * bs + L.a] = static_cast<VT>(d);
 }
 
-// The interpolation e = P e_c and the first F sweep in one launch (small
-// levels, where launches cost more than their work): e0 = P e_c on every row;
-// e1 = D^{-1}(r - sum_{J != I} A_IJ e0_J) on F rows, e1 = e0 on C rows --
-// what the two kernels leave, computed in the same order.
-template <int BS, typename MT, typename VT>
-__global__ __launch_bounds__(kThreads) void k_relax_interp(const int *__restrict__ rowptr,
-                                                          const int *__restrict__ colidx, const MT *__restrict__ vals,
-                                                          const double *__restrict__ dinv, int nb, int bs_rt, int G,
-                                                          const VT *__restrict__ r, const int *__restrict__ pmap,
-                                                          const VT *__restrict__ ec, const int8_t *__restrict__ cf,
-                                                          VT *__restrict__ e0, VT *__restrict__ e1, Gate gate) {
+// F sweep over the short rows of a small level (ShortRows): FIRST from e = P e_c,
+// the F rows' workgroups (wgF) followed by those that copy e_c to the C rows of e0
+// and e1; else from e0.  Either way e1_I = D_I^{-1}(r_I - sum_{J != I} A_IJ e_J) on
+// F rows.  Bound by latency: the header and the columns load first, everything
+// else one step later.  Reading the F list, A's rows and the one-point map in turn
+// instead (a launch at Q2 waited for five to six loads, 4.5 us a sweep and 6 us the
+// first) made an F-cycle solve of Q2 160^2 22.1 ms, where this takes 20.6.
+template <int BS, typename MT, typename VT, bool FIRST>
+__global__ __launch_bounds__(kThreads) void k_short_sweep(const int4 *__restrict__ hdr, const int2 *__restrict__ ent,
+                                                         const int *__restrict__ colidx,
+                                                         const int *__restrict__ pmap, const MT *__restrict__ vals,
+                                                         const double *__restrict__ dinv, int nF, int wgF, int bs_rt,
+                                                         int G, const VT *__restrict__ r, const VT *__restrict__ ec,
+                                                         const int *__restrict__ cpts, int nc, VT *__restrict__ e0,
+                                                         VT *__restrict__ e1, Gate gate) {
     __shared__ double part[kThreads];
     __shared__ double tb[kThreads];
     const int bs = Bs<BS>::get(bs_rt);
-    const Lane L = lane_of(G, bs);
-    int I = blockIdx.x * (kThreads / (G * bs)) + L.lr;
-    if (!L.valid || I >= nb || !live(gate, I)) I = -1;
-    const bool upd = I >= 0 && cf[I] == 0;
-    const PmapSrc<VT> src{ec, pmap, bs};
-    double acc = upd ? row_part_src<BS, MT, VT, PmapSrc<VT>, true>(colidx, vals, rowptr[I], rowptr[I + 1], L.g, G,
-                                                                   L.a, bs, src, I)
-                     : 0.0;
-    acc = reduce_groups(acc, L, G, bs, part);
-    const int64_t o = static_cast<int64_t>(I) * bs + L.a;
-    VT v = VT(0);
-    if (I >= 0 && L.g == 0) {
-        const int p = pmap[I];
-        v = p >= 0 ? ec[static_cast<int64_t>(p) * bs + L.a] : VT(0);
-        if (upd) tb[L.lr * bs + L.a] = static_cast<double>(r[o]) - acc;
+    if (FIRST && static_cast<int>(blockIdx.x) >= wgF) {
+        const int64_t g = static_cast<int64_t>(blockIdx.x - wgF) * kThreads + threadIdx.x;
+        split_c_rows(g, ec, cpts, nc, bs, e0, gate);
+        split_c_rows(g, ec, cpts, nc, bs, e1, gate);
+        return;
     }
-    __syncthreads();
+    const Lane L = lane_of(G, bs);
+    const int f = blockIdx.x * (kThreads / (G * bs)) + L.lr;
+    const bool in = L.valid && f < nF;
+    int4 h{-1, 0, 0, 0};
+    int2 c0{0, -1};
+    const int2 *cols = ent + static_cast<int64_t>(f) * kShort;
+    if (in) {
+        h = hdr[f];
+        c0 = L.g < kShort ? cols[L.g] : int2{0, -1};
+    }
+    const int I = in && live(gate, h.x) ? h.x : -1;
+    const int64_t o = static_cast<int64_t>(I) * bs + L.a;
+    DinvRow<BS, false, true> dr;
+    const double *D = dinv + static_cast<int64_t>(I) * bs * bs;
+    double rv = 0.0;
     if (I >= 0 && L.g == 0) {
-        e0[o] = v;
-        if (upd) {
-            const double d = apply_dinv<BS, false>(dinv + static_cast<int64_t>(I) * bs * bs, tb + L.lr * bs, L.a, bs);
-            e1[o] = static_cast<VT>(d);
-        } else {
-            e1[o] = v;
+        rv = static_cast<double>(r[o]);
+        dr.load(D, L.a);
+    }
+    double acc = 0.0;
+    if (I >= 0) {
+        for (int k = L.g; k < h.y; k += G) {
+            const int t = h.z + k + (k >= h.w ? 1 : 0);
+            int J;
+            if (k < kShort) {
+                const int2 c = k == L.g ? c0 : cols[k];
+                J = FIRST ? c.y : c.x;
+            } else {
+                J = FIRST ? pmap[colidx[t]] : colidx[t];
+            }
+            if (FIRST && J < 0) continue;
+            acc += block_row_dot<BS>(vals + (static_cast<int64_t>(t) * bs + L.a) * bs,
+                                     (FIRST ? ec : e0) + static_cast<int64_t>(J) * bs, bs);
         }
     }
+    acc = reduce_groups(acc, L, G, bs, part);
+    if (I >= 0 && L.g == 0) tb[L.lr * bs + L.a] = rv - acc;
+    __syncthreads();
+    if (I >= 0 && L.g == 0) e1[o] = static_cast<VT>(dr.apply(D, tb + L.lr * bs, L.a, bs));
+}
+
+// rc_i = r_C + sum_t Z_it r over Z's short rows
+template <int BS, typename MT, typename VT>
+__global__ __launch_bounds__(kThreads) void k_short_restrict(const int4 *__restrict__ zhdr,
+                                                            const int *__restrict__ zent,
+                                                            const int *__restrict__ zcol,
+                                                            const MT *__restrict__ zval, int nc, int bs_rt, int G,
+                                                            const VT *__restrict__ r, VT *__restrict__ rc,
+                                                            Gate gate) {
+    __shared__ double part[kThreads];
+    const int bs = Bs<BS>::get(bs_rt);
+    const Lane L = lane_of(G, bs);
+    const int i = blockIdx.x * (kThreads / (G * bs)) + L.lr;
+    const bool in = L.valid && i < nc;
+    int4 h{-1, 0, 0, 0};
+    int c0 = 0;
+    const int *cols = zent + static_cast<int64_t>(i) * kShort;
+    if (in) {
+        h = zhdr[i];
+        c0 = L.g < kShort ? cols[L.g] : 0;
+    }
+    const bool act = in && live(gate, i);
+    double rv = 0.0;
+    if (act && L.g == 0) rv = static_cast<double>(r[static_cast<int64_t>(h.x) * bs + L.a]);
+    double acc = 0.0;
+    if (act) {
+        for (int k = L.g; k < h.y; k += G) {
+            const int t = h.z + k;
+            const int J = k < kShort ? (k == L.g ? c0 : cols[k]) : zcol[t];
+            acc += block_row_dot<BS>(zval + (static_cast<int64_t>(t) * bs + L.a) * bs, r + static_cast<int64_t>(J) * bs,
+                                     bs);
+        }
+    }
+    acc = reduce_groups(acc, L, G, bs, part);
+    if (act && L.g == 0) rc[static_cast<int64_t>(i) * bs + L.a] = static_cast<VT>(rv + acc);
 }
 
 // rc_i = r_{cpts[i]} + sum_t Z_it r_{col t} (RB: Z's blocks by their nonzero rows)
@@ -1872,6 +1899,56 @@ void launch_split_next(const SplitView<MT> &S, int bs, int64_t nnzb, int nb, int
 }
 #undef NAIR_SPLIT_CR
 
+#define NAIR_SHORT_DISPATCH(bs, FIRST, ...)                                   \
+    switch (bs) {                                                             \
+        case 1: k_short_sweep<1, MT, VT, FIRST> __VA_ARGS__; break;           \
+        case 4: k_short_sweep<4, MT, VT, FIRST> __VA_ARGS__; break;           \
+        case 9: k_short_sweep<9, MT, VT, FIRST> __VA_ARGS__; break;           \
+        case 16: k_short_sweep<16, MT, VT, FIRST> __VA_ARGS__; break;         \
+        case 25: k_short_sweep<25, MT, VT, FIRST> __VA_ARGS__; break;         \
+        default: k_short_sweep<0, MT, VT, FIRST> __VA_ARGS__; break;          \
+    }
+
+template <typename MT, typename VT>
+void launch_short_sweep(const MatView<MT> &A, const ShortRows &S, int nF, bool first, const double *dinv, const VT *r,
+                        const VT *ec, const int *pmap, const int *cpts, int nc, VT *e0, VT *e1, hipStream_t s, Gate gate) {
+    need(A, "launch_short_sweep");
+    if (!S.on || !A.vals || A.bs > 32) fail(NAIR_EDEVICE, "launch_short_sweep: the level keeps no short rows");
+    const int G = groups_for(A);
+    const unsigned wgF = grid_rows(nF, G, A.bs);
+    const unsigned grid = wgF + (first ? grid_for(static_cast<int64_t>(nc) * A.bs, kThreads) : 0u);
+    if (first)
+        NAIR_SHORT_DISPATCH(A.bs, true, <<<grid, kThreads, 0, s>>>(S.hdr.get(), S.ent.get(), A.colidx, pmap, A.vals,
+                                                                   dinv, nF, static_cast<int>(wgF), A.bs, G, r, ec,
+                                                                   cpts, nc, e0, e1, gate))
+    else
+        NAIR_SHORT_DISPATCH(A.bs, false, <<<grid, kThreads, 0, s>>>(S.hdr.get(), S.ent.get(), A.colidx, pmap, A.vals,
+                                                                    dinv, nF, static_cast<int>(wgF), A.bs, G, r, ec,
+                                                                    cpts, nc, e0, e1, gate))
+    NAIR_HIP(hipGetLastError());
+}
+
+template <typename MT, typename VT>
+void launch_short_restrict(const MatView<MT> &Z, const ShortRows &S, const VT *r, VT *rc, hipStream_t s, Gate gate) {
+    if (!S.on || !Z.colidx || !Z.vals || Z.bs > 32) fail(NAIR_EDEVICE, "launch_short_restrict: the level keeps no short rows");
+    if (Z.nb <= 0) return;
+    const int G = groups_for(Z);
+    const unsigned grid = grid_rows(Z.nb, G, Z.bs);
+#define NAIR_SR(BS)                                                                                              \
+    k_short_restrict<BS, MT, VT><<<grid, kThreads, 0, s>>>(S.zhdr.get(), S.zent.get(), Z.colidx, Z.vals, Z.nb,   \
+                                                           Z.bs, G, r, rc, gate)
+    switch (Z.bs) {
+        case 1: NAIR_SR(1); break;
+        case 4: NAIR_SR(4); break;
+        case 9: NAIR_SR(9); break;
+        case 16: NAIR_SR(16); break;
+        case 25: NAIR_SR(25); break;
+        default: NAIR_SR(0); break;
+    }
+#undef NAIR_SR
+    NAIR_HIP(hipGetLastError());
+}
+
 template <typename VT>
 void launch_relax_T_first(const double *dinv, const VT *r, const int8_t *cf, VT *e0, VT *e1, int nb, int bs,
                           hipStream_t s, Gate gate) {
@@ -1927,18 +2004,6 @@ template <typename VT>
 void launch_interp(const int *pmap, const VT *ec, VT *e0, VT *e1, int nb, int bs, hipStream_t s, Gate gate) {
     k_interp<VT><<<grid_for(static_cast<int64_t>(nb) * bs, kThreads), kThreads, 0, s>>>(pmap, ec, e0, e1, nb, bs,
                                                                                          gate);
-    NAIR_HIP(hipGetLastError());
-}
-
-template <typename MT, typename VT>
-void launch_relax_interp(const MatView<MT> &A, const double *dinv, const VT *r, const int *pmap, const VT *ec,
-                         const int8_t *cf, VT *e0, VT *e1, hipStream_t s, Gate gate) {
-    need(A, "launch_relax_interp");
-    if (A.nb <= 0) return;
-    const int G = groups_for(A);
-    const unsigned grid = grid_rows(A.nb, G, A.bs);
-    NAIR_BS_DISPATCH(A.bs, k_relax_interp, <<<grid, kThreads, 0, s>>>(A.rowptr, A.colidx, A.vals, dinv, A.nb, A.bs,
-                                                                      G, r, pmap, ec, cf, e0, e1, gate));
     NAIR_HIP(hipGetLastError());
 }
 
@@ -2095,14 +2160,17 @@ void launch_to_float(const double *in, float *out, int64_t n, hipStream_t s, con
                                           Gate);                                                                     \
     template void launch_relax<MT, VT>(const MatView<MT> &, const double *, bool, const VT *, const VT *, VT *,      \
                                        const int *, int, const int8_t *, int, hipStream_t, Gate, bool);              \
+    template void launch_short_sweep<MT, VT>(const MatView<MT> &, const ShortRows &, int, bool, const double *,      \
+                                             const VT *, const VT *, const int *, const int *, int, VT *, VT *,      \
+                                             hipStream_t, Gate);                                                     \
+    template void launch_short_restrict<MT, VT>(const MatView<MT> &, const ShortRows &, const VT *, VT *,            \
+                                                hipStream_t, Gate);                                                  \
     template void launch_split_first<MT, VT>(const SplitView<MT> &, int, int64_t, int, int, const VT *, const VT *,  \
                                              VT *, VT *, const int *, int, VT *, hipStream_t, Gate);                 \
     template void launch_split_next<MT, VT>(const SplitView<MT> &, int, int64_t, int, int, int, int, const VT *,     \
                                             VT *, hipStream_t, Gate);                                                \
     template void launch_restrict<MT, VT>(const MatView<MT> &, const VT *, const int *, VT *, hipStream_t, Gate);    \
     template void launch_interp<VT>(const int *, const VT *, VT *, VT *, int, int, hipStream_t, Gate);               \
-    template void launch_relax_interp<MT, VT>(const MatView<MT> &, const double *, const VT *, const int *,          \
-                                              const VT *, const int8_t *, VT *, VT *, hipStream_t, Gate);            \
     template void launch_relax_T_first<VT>(const double *, const VT *, const int8_t *, VT *, VT *, int, int,         \
                                            hipStream_t, Gate);                                                       \
     template void launch_restrict_T<VT>(const int *, const int *, const VT *, VT *, int, int, hipStream_t, Gate);    \

@@ -71,6 +71,7 @@ struct Level {
     // (A's on the levels of at least kFewLanes lanes: as a split copy)
     SweepCopy sweep, sweepT;
     SplitCopy split;
+    ShortRows shortr;               // levels below kFewLanes lanes
     // Z's blocks by their nonzero rows, for the restriction (levels with sweep copies)
     RowBlocks zrows;
     // bit masks of the nonzero rows of Z's and A's blocks, where the kernels

@@ -136,6 +136,17 @@ void split(Hier &h, Level &L, int lvl, hipStream_t s, const std::function<void()
     }
 }
 
+// Short rows of the small levels that a cycle visits one by one (not those below
+// the collapsed coarse solve, nor those that are to have sweep copies)
+static void build_short(Hier &h, hipStream_t s) {
+    const int last = h.collapse > 0 ? h.collapse : static_cast<int>(h.lv.size()) - 1;
+    for (int l = 0; l < last && h.prm.sweep_copy != 1; ++l) {
+        Level &L = *h.lv[l];
+        if (!L.coarsest && few_lanes(L.A.nb, L.A.bs))
+            build_short_rows(L.A, L.Z, L.flist.get(), L.nF, L.cpts.get(), L.nc, L.pmap.get(), L.shortr, s);
+    }
+}
+
 }  // namespace
 
 void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const int *rowptr, const int *colidx,
@@ -471,6 +482,7 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
     // the finest operator is read by every cycle: a compact copy of its face blocks
     if (p.faces == 1 && p.form == 0) build_face(h.lv[0]->A, h.lv[0]->face, s, &h.lv[0]->facemeta);
     build_collapse(h, s);
+    build_short(h, s);
     build_sweeps(h, false, s);
     if (p.precision == 1) make_fp32_copies(h, s);
     prepare_cycle(h, false, s);   // the F-cycle's saved vectors

@@ -25,6 +25,9 @@ template <>
 struct Store<double> {
     static MatView<double> A(const Level &L) { return op_view(L, false).with_groups(L.tune[TU_RELAX]); }
     static SplitView<double> split(const Level &L) { return split_view(L); }
+    // A and Z by their whole blocks
+    static MatView<double> Ab(const Level &L) { return view(L.A).with_groups(L.tune[TU_RELAX]); }
+    static MatView<double> Zb(const Level &L) { return view(L.Z).with_groups(L.tune[TU_RESTRICT]); }
     static MatView<double> Z(const Level &L) { return z_view(L).with_groups(L.tune[TU_RESTRICT]); }
     static MatView<double> AT(const Level &L) { return op_view(L, true).with_groups(L.tune[TU_RELAX_T]); }
     static MatView<double> ZT(const Level &L) { return view(L.ZT).with_groups(L.tune[TU_INTERP_T]); }
@@ -44,6 +47,8 @@ template <>
 struct Store<float> {
     static MatView<float> A(const Level &L) { return op_view32(L, false).with_groups(L.tune[TU_RELAX]); }
     static SplitView<float> split(const Level &L) { return split_view32(L); }
+    static MatView<float> Ab(const Level &L) { return view(L.A, L.vals32.get()).with_groups(L.tune[TU_RELAX]); }
+    static MatView<float> Zb(const Level &L) { return view(L.Z, L.z32.get()).with_groups(L.tune[TU_RESTRICT]); }
     static MatView<float> Z(const Level &L) { return z_view32(L).with_groups(L.tune[TU_RESTRICT]); }
     static MatView<float> AT(const Level &L) { return op_view32(L, true).with_groups(L.tune[TU_RELAX_T]); }
     static MatView<float> ZT(const Level &L) { return view(L.ZT, L.zt32.get()).with_groups(L.tune[TU_INTERP_T]); }
@@ -94,7 +99,10 @@ const T *cycle(Hier &h, int l, bool fcyc, hipStream_t s) {
     Level &C = *h.lv[l + 1];
     {
         TimerScope ts(TK_RESTRICT, l, s);
-        launch_restrict<T, T>(S::Z(L), S::r(L), L.cpts.get(), S::r(C), s, gate(h, C));
+        if (L.shortr.on)
+            launch_short_restrict<T, T>(S::Zb(L), L.shortr, S::r(L), S::r(C), s, gate(h, C));
+        else
+            launch_restrict<T, T>(S::Z(L), S::r(L), L.cpts.get(), S::r(C), s, gate(h, C));
     }
     const T *ec = coarse_solve<T>(h, l + 1, fcyc, s);
     const bool small = few_lanes(L.A.nb, bs);
@@ -118,24 +126,19 @@ const T *cycle(Hier &h, int l, bool fcyc, hipStream_t s) {
         cur = nu % 2 == 1 ? e1 : e2;
         oth = nu % 2 == 1 ? e2 : e1;
     } else {
-        // on a small level the interpolation rides along with the first sweep
-        const bool fuse = small && !L.face.on;
-        if (!fuse) {
+        if (!L.shortr.on) {
             TimerScope ts(TK_INTERP, l, s);
             launch_interp<T>(L.pmap.get(), ec, S::e0(L), S::e1(L), L.A.nb, bs, s, gate(h, L));
         }
         // the nu sweeps run back to back; one event pair brackets the group
         TimerScope ts(TK_RELAX, l, s, h.prm.degree + 1);
-        int k = 0;
-        if (fuse) {
-            launch_relax_interp<T, T>(A, L.dinv.get(), S::r(L), L.pmap.get(), ec, L.cf.get(), cur, oth, s,
-                                      gate(h, L));
-            std::swap(cur, oth);
-            k = 1;
-        }
-        for (; k <= h.prm.degree; ++k) {
-            launch_relax<T, T>(A, L.dinv.get(), false, S::r(L), cur, oth, L.flist.get(), L.nF, L.cf.get(), 0, s,
-                               gate(h, L), !small);
+        for (int k = 0; k <= h.prm.degree; ++k) {
+            if (L.shortr.on)   // (the interpolation rides along with the first sweep)
+                launch_short_sweep<T, T>(S::Ab(L), L.shortr, L.nF, k == 0, L.dinv.get(), S::r(L), ec, L.pmap.get(),
+                                         L.cpts.get(), L.nc, cur, oth, s, gate(h, L));
+            else
+                launch_relax<T, T>(A, L.dinv.get(), false, S::r(L), cur, oth, L.flist.get(), L.nF, L.cf.get(), 0, s,
+                                   gate(h, L), !small);
             std::swap(cur, oth);
         }
     }

@@ -284,7 +284,49 @@ __global__ __launch_bounds__(256) void k_split_dinv(const double *__restrict__ d
     }
 }
 
+// Headers and columns of F rows f < nF and of Z's rows i < nc (ShortRows): one thread per row.
+__global__ __launch_bounds__(256) void k_short_rows(const int *__restrict__ rowptr, const int *__restrict__ colidx,
+                                                   const int *__restrict__ flist, int nF,
+                                                   const int *__restrict__ pmap, const int *__restrict__ zrp,
+                                                   const int *__restrict__ zcol, const int *__restrict__ cpts, int nc,
+                                                   int4 *__restrict__ hdr, int2 *__restrict__ ent,
+                                                   int4 *__restrict__ zhdr, int *__restrict__ zent) {
+    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g < nF) {
+        const int I = flist[g], lo = rowptr[I], hi = rowptr[I + 1];
+        int n = 0, before = 0;
+        for (int t = lo; t < hi; ++t) {
+            const int J = colidx[t];
+            if (J == I) continue;
+            if (J < I) ++before;
+            if (n < kShort) ent[static_cast<int64_t>(g) * kShort + n] = int2{J, pmap[J]};
+            ++n;
+        }
+        for (int k = n; k < kShort; ++k) ent[static_cast<int64_t>(g) * kShort + k] = int2{0, -1};
+        hdr[g] = int4{I, n, lo, before};
+    } else if (g - nF < nc) {
+        const int i = g - nF, lo = zrp[i], n = zrp[i + 1] - lo;
+        for (int k = 0; k < kShort; ++k) zent[static_cast<int64_t>(i) * kShort + k] = k < n ? zcol[lo + k] : 0;
+        zhdr[i] = int4{cpts[i], n, lo, 0};
+    }
+}
+
 }  // namespace
+
+void build_short_rows(const DevBSR &A, const DevBSR &Z, const int *flist, int nF, const int *cpts, int nc,
+                      const int *pmap, ShortRows &S, hipStream_t s) {
+    S = ShortRows();
+    if (nF <= 0 || nc <= 0 || A.bs > 32) return;
+    S.hdr.alloc(static_cast<size_t>(nF));
+    S.ent.alloc(static_cast<size_t>(nF) * kShort);
+    S.zhdr.alloc(static_cast<size_t>(nc));
+    S.zent.alloc(static_cast<size_t>(nc) * kShort);
+    k_short_rows<<<grid_for(static_cast<int64_t>(nF) + nc, 256), 256, 0, s>>>(
+        A.rowptr.get(), A.colidx.get(), flist, nF, pmap, Z.rowptr.get(), Z.colidx.get(), cpts, nc, S.hdr.get(),
+        S.ent.get(), S.zhdr.get(), S.zent.get());
+    NAIR_HIP(hipGetLastError());
+    S.on = true;
+}
 
 void order_by_depth(const DevBSR &A, const int8_t *cf, DBuf<int> &flist, int nF, int *counts, hipStream_t s) {
     DBuf<int> flag(static_cast<size_t>(nF) * 3), pos(static_cast<size_t>(nF) * 3 + 1), out(static_cast<size_t>(nF));
