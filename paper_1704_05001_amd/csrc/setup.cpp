@@ -98,10 +98,35 @@ void make_direct(Level &L, int lvl, hipStream_t s) {
 // C/F splitting by independent-set rounds; state ends as 1 (C) / 0 (F) in L.cf.
 // After each batch of rounds `enqueue` launches work whose results `extra`
 // reads back with the round counts (the last batch's are what the caller gets).
-void split(Hier &h, Level &L, int lvl, hipStream_t s, const std::function<void()> &enqueue,
+// A small level takes one launch, which also gives cscan (enqueue(true): done
+// already) and, with no directly solved system on it, cidx, cpts and flist
+// (returns whether it did); its launches and gaps, about 25 of 10 us a level,
+// were a fifth of a small problem's setup.
+bool split(Hier &h, Level &L, int lvl, hipStream_t s, int *cscan, const std::function<void(bool)> &enqueue,
            const std::vector<ReadItem> &extra) {
     const int n = L.A.nb;
     const int64_t nz = L.A.bound();
+    if (split_small_rows(n)) {
+        const bool index = !L.direct.get();
+        if (index) {
+            L.cpts.alloc(n);
+            L.flist.alloc(n);
+        }
+        DBuf<int> out(2);
+        launch_split_small(L.A.rowptr.get(), L.A.colidx.get(), L.mask.get(), L.lambda.get(), L.lbase.get(),
+                           L.direct.get(), n, nz, h.prm.seed, lvl, kMaxRounds, L.cf.get(), L.dround.get(), cscan,
+                           index ? L.cidx.get() : nullptr, L.cpts.get(), L.flist.get(), out.get(), s);
+        enqueue(true);
+        int res = 0;
+        std::vector<ReadItem> items{{out.get(), &res, sizeof(int)}};
+        items.insert(items.end(), extra.begin(), extra.end());
+        read_device(items.data(), items.size(), s);
+        if (res == -2) fail(NAIR_ECOARSEN, "splitting did not finish");
+        if (res >= 0) {
+            L.rounds = res;
+            return index;
+        }
+    }
     DBuf<int> stptr(static_cast<size_t>(n) + 1), fill(n), stidx(nz > 0 ? nz : 1);
     DBuf<int8_t> newc(n);
     DBuf<int> counts(kMaxRounds + 1);
@@ -123,14 +148,14 @@ void split(Hier &h, Level &L, int lvl, hipStream_t s, const std::function<void()
                               L.dround.get(), counts.get() + r, s);
         }
         int hc[kRoundBatch + 1];
-        enqueue();
+        enqueue(false);
         std::vector<ReadItem> items{{counts.get() + first, hc, sizeof(hc)}};
         items.insert(items.end(), extra.begin(), extra.end());
         read_device(items.data(), items.size(), s);
         for (int b = 0; b <= kRoundBatch; ++b)
             if (hc[b] == 0) {
                 L.rounds = first + b;   // 0: nothing was undecided at the start
-                return;
+                return false;
             }
         if (r + kRoundBatch > kMaxRounds) fail(NAIR_ECOARSEN, "splitting did not finish");
     }
@@ -289,9 +314,11 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
         std::vector<int> cseg(nsys + 2);   // coarse blocks per system, as offsets; then the singular flag
         DBuf<int> cseg_d(nsys + 2);
         cseg[0] = 0;
-        auto count_c_launch = [&]() {
-            launch_cf_flags(L.cf.get(), n, 1, cflag.get(), s);
-            scan_exclusive(cflag.get(), cscan.get(), n, s);
+        auto count_c_launch = [&](bool scanned) {
+            if (!scanned) {
+                launch_cf_flags(L.cf.get(), n, 1, cflag.get(), s);
+                scan_exclusive(cflag.get(), cscan.get(), n, s);
+            }
             if (nsys == 1) return;   // one system: its C count is the scan's total
             launch_gather_int(cscan.get(), L.seg_d.get(), nsys + 1, cseg_d.get(), s);
             NAIR_HIP(hipMemcpyAsync(cseg_d.get() + nsys + 1, sing.get(), sizeof(int), hipMemcpyDeviceToDevice, s));
@@ -301,14 +328,15 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
                                               {sing.get(), &cseg[2], sizeof(int)}}
                       : std::vector<ReadItem>{{cseg_d.get(), cseg.data(), sizeof(int) * (nsys + 2)}};
         auto count_c = [&]() {
-            count_c_launch();
+            count_c_launch(false);
             read_device(count_c_items.data(), count_c_items.size(), s);
         };
         int anz = 0;
         std::vector<ReadItem> split_items = count_c_items;
         if (L.A.nnzb < 0) split_items.push_back({L.A.rowptr.get() + n, &anz, sizeof(int)});
+        bool indexed = false;   // cidx, cpts and flist came with the splitting
         if (l == 0 && p.cf_override_host) count_c();
-        else split(h, L, l, s, count_c_launch, split_items);
+        else indexed = split(h, L, l, s, cscan.get(), count_c_launch, split_items);
         if (L.A.nnzb < 0) L.A.nnzb = anz;
         const int hsing = cseg[nsys + 1];
         if (hsing != kNoSingular)
@@ -354,9 +382,11 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
         } else {
             L.nF = n - nc;
         }
-        L.cpts.alloc(nc);
-        L.flist.alloc(L.nF);
-        launch_cf_index(L.cf.get(), cscan.get(), fscan.get(), n, L.cidx.get(), L.cpts.get(), L.flist.get(), s);
+        if (!indexed || ndir > 0) {
+            L.cpts.alloc(nc);
+            L.flist.alloc(L.nF);
+            launch_cf_index(L.cf.get(), cscan.get(), fscan.get(), n, L.cidx.get(), L.cpts.get(), L.flist.get(), s);
+        }
         launch_one_point(L.A.rowptr.get(), L.A.colidx.get(), L.bnorm.get(), L.cf.get(), L.cidx.get(), n,
                          L.pmap.get(), L.margin.get(), s);
         // Neumann operands: T (phi-strong F-F, scaled by -D_ff^{-1}) and W_0 = A_cf

@@ -569,6 +569,184 @@ __global__ __launch_bounds__(256) void k_pmis_update(const int *__restrict__ row
     atomicAdd(undecided, 1);
 }
 
+// The whole splitting of a level of at most kSplitRows blocks in one workgroup:
+// states, every round, and the numbering of the result (cscan[0..nb], cidx, cpts,
+// flist when asked for).  Keys, states and the strong couplings (16-bit columns)
+// lie in LDS; a thread keeps R consecutive rows, so the numbering is one scan over
+// the threads.  A strong coupling whose two ends are undecided marks the end with
+// the smaller key, which covers S and S^T without S^T's lists.  out = {rounds, C
+// blocks}; rounds -1: the couplings do not fit LDS and nothing was written, -2:
+// max_rounds were not enough.  Bound by the latency of one workgroup (the lists
+// load once, a round is LDS only).
+constexpr int kSplitRows = 4096;
+constexpr int kSplitThreads = 1024;
+constexpr int kSplitLds = 156 * 1024;   // (160 KiB less the scans' words)
+
+__device__ inline int split_scan(int v, int *wsum, int &total) {   // exclusive scan over the workgroup
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int x = v;
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(x, d);
+        if (lane >= d) x += y;
+    }
+    __syncthreads();   // (wsum free again)
+    if (lane == 63) wsum[w] = x;
+    __syncthreads();
+    int before = 0;
+    total = 0;
+    for (int k = 0; k < kSplitThreads / 64; ++k) {
+        if (k < w) before += wsum[k];
+        total += wsum[k];
+    }
+    return before + x - v;
+}
+
+template <int R>
+__global__ __launch_bounds__(kSplitThreads) void k_split_small(
+    const int *__restrict__ rowptr, const int *__restrict__ colidx, const uint8_t *__restrict__ mask,
+    const int *__restrict__ lambda, const int *__restrict__ lbase, const int8_t *__restrict__ direct, int nb,
+    uint64_t seed, int level, int max_rounds, int ecap, int8_t *__restrict__ cf, int *__restrict__ dround,
+    int *__restrict__ cscan, int *__restrict__ cidx, int *__restrict__ cpts, int *__restrict__ flist,
+    int *__restrict__ out) {
+    extern __shared__ uint64_t hash[];                       // [nb]
+    int *lam = reinterpret_cast<int *>(hash + nb);           // [nb]
+    int8_t *st = reinterpret_cast<int8_t *>(lam + nb);       // [nb] states
+    int8_t *bt = st + nb;                                    // [nb] 1: a neighbour's key is larger
+    uint16_t *edge = reinterpret_cast<uint16_t *>(bt + nb);  // [ecap] (nb * 14 bytes before it: even)
+    __shared__ int wsum[kSplitThreads / 64];
+    const int I0 = threadIdx.x * R;
+    const uint64_t salt = seed ^ (static_cast<uint64_t>(level) << 40);
+    int lo[R], hi[R], e0[R + 1], rnd[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int I = I0 + k;
+        rnd[k] = 0;
+        lo[k] = I < nb ? rowptr[I] : 0;
+        hi[k] = I < nb ? rowptr[I + 1] : 0;
+        if (I < nb) {
+            const int l = lambda[I];
+            lam[I] = l;
+            hash[I] = splitmix64(salt ^ static_cast<uint64_t>(I - (lbase ? lbase[I] : 0)));
+            st[I] = direct && direct[I] ? kD : (l != 0 ? kUnd : kF);
+            bt[I] = 0;
+        }
+    }
+    int count = 0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        e0[k] = count;
+        for (int t = lo[k]; t < hi[k]; t += 8) {
+            int m[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) m[j] = mask[min(t + j, hi[k] - 1)];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) count += (t + j < hi[k] && (m[j] & 1)) ? 1 : 0;
+        }
+    }
+    e0[R] = count;
+    int total;
+    const int base = split_scan(count, wsum, total);
+    if (total > ecap) {
+        if (threadIdx.x == 0) out[0] = -1;
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        int o = base + e0[k];
+        for (int t = lo[k]; t < hi[k]; t += 8) {
+            int m[8], c[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int u = min(t + j, hi[k] - 1);
+                m[j] = mask[u];
+                c[j] = colidx[u];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (t + j < hi[k] && (m[j] & 1)) edge[o++] = static_cast<uint16_t>(c[j]);
+        }
+    }
+    int und = 0;
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+        if (I0 + k < nb && st[I0 + k] == kUnd) und = 1;
+    int round = 0;
+    und = __syncthreads_or(und);
+    while (und && round < max_rounds) {
+        ++round;
+        // every coupling between undecided blocks marks its smaller end
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int I = I0 + k;
+            if (I >= nb || st[I] != kUnd) continue;
+            const int lamI = lam[I];
+            const uint64_t hI = hash[I];
+            for (int e = base + e0[k]; e < base + e0[k + 1]; ++e) {
+                const int J = edge[e];
+                if (st[J] != kUnd) continue;
+                bt[key_beats(lamI, hI, I, lam[J], hash[J], J) ? J : I] = 1;
+            }
+        }
+        __syncthreads();
+        // unmarked blocks become C; marked ones that depend strongly on one become F
+        // (a state that changes here belongs to a marked block, which is no new C either way)
+        bool c[R];
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int I = I0 + k;
+            c[k] = false;
+            if (I >= nb || st[I] != kUnd) continue;
+            c[k] = bt[I] == 0;
+            if (c[k]) continue;
+            bool f = false;
+            for (int e = base + e0[k]; e < base + e0[k + 1] && !f; ++e) f = st[edge[e]] == kUnd && bt[edge[e]] == 0;
+            if (f) {
+                st[I] = kF;
+                rnd[k] = round;
+            }
+        }
+        __syncthreads();
+        und = 0;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int I = I0 + k;
+            if (I >= nb) continue;
+            if (c[k]) {
+                st[I] = kC;
+                rnd[k] = round;
+            }
+            bt[I] = 0;
+            if (st[I] == kUnd) und = 1;
+        }
+        und = __syncthreads_or(und);
+    }
+    int nc = 0;
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+        if (I0 + k < nb && st[I0 + k] == kC) ++nc;
+    int o = split_scan(nc, wsum, total);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int I = I0 + k;
+        if (I >= nb) continue;
+        const int8_t v = st[I];
+        cf[I] = v;
+        dround[I] = rnd[k];
+        cscan[I] = o;
+        if (cidx) {
+            cidx[I] = v == kC ? o : -1;
+            if (v == kC) cpts[o] = I;
+            else flist[I - o] = I;
+        }
+        if (v == kC) ++o;
+    }
+    if (threadIdx.x == 0) {
+        cscan[nb] = total;
+        out[0] = und ? -2 : round;
+        out[1] = total;
+    }
+}
+
 __global__ __launch_bounds__(256) void k_cf_flags(const int8_t *__restrict__ state, int nb, int8_t want,
                                                  int *__restrict__ flags) {
     const int I = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1074,6 +1252,36 @@ void launch_pmis_round(const int *rowptr, const int *colidx, const uint8_t *mask
                                                     level, state, newc, undecided - 1);
     k_pmis_update<<<grid_for(nb, 256), 256, 0, s>>>(rowptr, colidx, mask, nb, round, state, newc, dround,
                                                     undecided);
+    NAIR_HIP(hipGetLastError());
+}
+
+// Whether k_split_small takes a level of nb blocks (and its LDS attribute could be set)
+bool split_small_rows(int nb) {
+    static const bool ok = [] {
+        bool all = true;
+        for (const void *f : {reinterpret_cast<const void *>(k_split_small<1>), reinterpret_cast<const void *>(k_split_small<2>),
+                              reinterpret_cast<const void *>(k_split_small<4>)})
+            all = all && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSplitLds) == hipSuccess;
+        if (!all) (void)hipGetLastError();
+        return all;
+    }();
+    return ok && nb > 0 && nb <= kSplitRows;
+}
+
+void launch_split_small(const int *rowptr, const int *colidx, const uint8_t *mask, const int *lambda, const int *lbase,
+                        const int8_t *direct, int nb, int64_t nz, uint64_t seed, int level, int max_rounds, int8_t *cf,
+                        int *dround, int *cscan, int *cidx, int *cpts, int *flist, int *out, hipStream_t s) {
+    if (!split_small_rows(nb)) fail(NAIR_EDEVICE, "launch_split_small: too many blocks");
+    const int fixed = nb * 14;   // hash, lambda, state, mark
+    const int ecap = static_cast<int>(std::min<int64_t>(nz, (kSplitLds - fixed) / 2));
+    const size_t lds = static_cast<size_t>(fixed) + 2 * static_cast<size_t>(ecap);
+#define NAIR_SPLIT(R)                                                                                               \
+    k_split_small<R><<<1, kSplitThreads, lds, s>>>(rowptr, colidx, mask, lambda, lbase, direct, nb, seed, level,    \
+                                                   max_rounds, ecap, cf, dround, cscan, cidx, cpts, flist, out)
+    if (nb <= kSplitThreads) NAIR_SPLIT(1);
+    else if (nb <= 2 * kSplitThreads) NAIR_SPLIT(2);
+    else NAIR_SPLIT(4);
+#undef NAIR_SPLIT
     NAIR_HIP(hipGetLastError());
 }
 
