@@ -142,6 +142,14 @@ struct ReadItem {
     void *host;
     size_t bytes;
 };
+// Words of several device arrays gathered into (pinned, coherent) host memory, then *word = ticket
+struct GatherJobs {
+    static constexpr int kMax = 8;
+    const uint32_t *src[kMax];
+    int words[kMax], at[kMax];
+    int k = 0;
+};
+void launch_gather_words(const GatherJobs &J, uint32_t *host, uint32_t *word, uint32_t ticket, hipStream_t s);
 void read_device(std::initializer_list<ReadItem> items, hipStream_t s);
 void read_device(const ReadItem *items, size_t nitems, hipStream_t s);
 int read_int(const int *dptr, hipStream_t s);

@@ -795,6 +795,16 @@ __global__ __launch_bounds__(256) void k_mark_direct(const int8_t *__restrict__ 
     if (I < nb && direct[I]) state[I] = kD;
 }
 
+// (one workgroup: the ticket goes out after every word is visible to the host)
+__global__ __launch_bounds__(256) void k_gather_words(GatherJobs J, uint32_t *__restrict__ host,
+                                                     uint32_t *__restrict__ word, uint32_t ticket) {
+    for (int k = 0; k < J.k; ++k)
+        for (int i = threadIdx.x; i < J.words[k]; i += blockDim.x) host[J.at[k] + i] = J.src[k][i];
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(word, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 struct FillJobs {
     int *p[4];
     int64_t n[4];
@@ -1282,6 +1292,11 @@ void launch_split_small(const int *rowptr, const int *colidx, const uint8_t *mas
     else if (nb <= 2 * kSplitThreads) NAIR_SPLIT(2);
     else NAIR_SPLIT(4);
 #undef NAIR_SPLIT
+    NAIR_HIP(hipGetLastError());
+}
+
+void launch_gather_words(const GatherJobs &J, uint32_t *host, uint32_t *word, uint32_t ticket, hipStream_t s) {
+    k_gather_words<<<1, 256, 0, s>>>(J, host, word, ticket);
     NAIR_HIP(hipGetLastError());
 }
 
