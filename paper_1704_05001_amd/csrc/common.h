@@ -17,8 +17,6 @@ constexpr int kMaxBs = 32;          // largest block size the kernels accept
 constexpr int kMaxLevels = 64;
 constexpr int kStallDenseDofs = 4096;
 constexpr int kMaxGmres = 200;      // longest GMRES restart cycle
-constexpr int kHashSmall = 2048;    // LDS hash slots of the per-wave symbolic kernels
-constexpr int kHashLarge = 8192;    // LDS hash slots of the per-workgroup fallback
 
 // ------------------------------------------------------------------ errors
 struct Error {

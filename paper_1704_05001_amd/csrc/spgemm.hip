@@ -1,6 +1,7 @@
-// Row-wise block SpGEMM (Gustavson order): LDS hash tables for the symbolic
-// phase (a row's products enumerated flat across a wave), per-output-block
-// pair lists in the fixed accumulation order, and numeric kernels that walk
+// Row-wise block SpGEMM (Gustavson order): the symbolic phase sorts a row's
+// products by (output column, number) within a group of lanes, which gives the
+// pattern and per-output-block
+// pair lists in the fixed accumulation order; and numeric kernels that walk
 // them (FP64 matrix cores for 9x9 and 16x16 blocks, one thread per block row
 // otherwise); union-add of two block matrices; and the Galerkin product
 // K = R A P with the one-point P and the drop filter.
@@ -24,12 +25,6 @@ namespace {
 
 constexpr int kWave = 64;
 
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Inclusive prefix sum of x over the wave's 64 lanes by DPP moves (no LDS
 // round trips): shifts by 1, 2, 4, 8 within each row of 16 lanes, then each
 // row's last lane added into the rows after it.  A lane whose source lies
@@ -48,70 +43,90 @@ __device__ inline int wave_incl_scan(int x) {
     return x;
 }
 
-// Sort a wave's n distinct keys list[0 .. n) ascending in place (n <= cap, the
-// list's room): up to 64 keys by rank (a key per lane), more by a bitonic
-// network over the next power of two, padded with INT_MAX.
-__device__ inline void wave_sort(int *list, int n, int cap, int lane) {
-    if (n <= kWave) {
-        const int k = lane < n ? list[lane] : 0;
-        int r = 0;
-        if (lane < n)
-            for (int b = 0; b < n; ++b) r += (list[b] < k) ? 1 : 0;
-        wave_sync();
-        if (lane < n) list[r] = k;
-        wave_sync();
-        return;
-    }
-    int n2 = kWave;
-    while (n2 < n) n2 <<= 1;
-    if (n2 > cap) n2 = cap;   // (n <= cap, a power of two)
-    for (int a = n + lane; a < n2; a += kWave) list[a] = INT_MAX;
-    wave_sync();
-    for (int k = 2; k <= n2; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int a = lane; a < n2; a += kWave) {
-                const int b = a ^ j;
-                if (b > a) {
-                    const int x = list[a], y = list[b];
-                    if ((x > y) == ((a & k) == 0)) {
-                        list[a] = y;
-                        list[b] = x;
-                    }
-                }
-            }
-            wave_sync();
+// ------------------------------------------------------------- key sorts
+
+// The value of lane (lane ^ D): within rows of 16 lanes by DPP moves.
+template <int D>
+__device__ inline uint32_t lane_xor32(uint32_t x) {
+    const int v = static_cast<int>(x);
+    if constexpr (D == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);   // quad_perm 1 0 3 2
+    if constexpr (D == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);   // quad_perm 2 3 0 1
+    if constexpr (D == 4)   // half rows mirrored (xor 7), then quads mirrored (xor 3)
+        return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true), 0x1B, 0xF,
+                                           0xF, true);
+    if constexpr (D == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);   // row_ror:8
+    return static_cast<uint32_t>(__shfl_xor(v, D, kWave));
+}
+template <int D>
+__device__ inline uint32_t lane_xor(uint32_t x) { return lane_xor32<D>(x); }
+template <int D>
+__device__ inline uint64_t lane_xor(uint64_t x) {
+    return static_cast<uint64_t>(lane_xor32<D>(static_cast<uint32_t>(x))) |
+           static_cast<uint64_t>(lane_xor32<D>(static_cast<uint32_t>(x >> 32))) << 32;
+}
+
+// Bitonic network over the W E keys of each group of W lanes, ascending; key
+// number s = lane * E + e.
+template <int E, int KK, int J, typename KEY>
+__device__ inline void sort_step(KEY (&key)[E], int gl) {
+    if constexpr (J >= E) {
+        const bool lower = (gl & (J / E)) == 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const KEY o = lane_xor<J / E>(key[e]);
+            const bool asc = ((gl * E + e) & KK) == 0;
+            key[e] = (lower == asc) == (o < key[e]) ? o : key[e];
         }
+    } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if (e & J) continue;
+            const KEY a = key[e], b = key[e | J];
+            const bool asc = ((gl * E + e) & KK) == 0;
+            key[e] = asc == (b < a) ? b : a;
+            key[e | J] = asc == (b < a) ? a : b;
+        }
+    }
+    if constexpr (J > 1) sort_step<E, KK, J / 2>(key, gl);
+}
+template <int W, int E, int KK = 2, typename KEY>
+__device__ inline void group_sort(KEY (&key)[E], int gl) {
+    sort_step<E, KK, KK / 2>(key, gl);
+    if constexpr (KK < W * E) group_sort<W, E, KK * 2>(key, gl);
 }
 
-constexpr int kEmpty = -1;
-
-__device__ inline bool hash_insert(int *table, int mask, int key) {
-    unsigned slot = (static_cast<unsigned>(key) * 2654435761u) & static_cast<unsigned>(mask);
-    while (true) {
-        int prev = atomicCAS(&table[slot], kEmpty, key);
-        if (prev == kEmpty) return true;
-        if (prev == key) return false;
-        slot = (slot + 1) & static_cast<unsigned>(mask);
+// A sorted group's keys are (column << B | place); a head is the first key of a
+// column.  heads(): how many the group has, and per key how many lie at or before it.
+template <int W, int E, int B, typename KEY>
+__device__ inline int heads(const KEY (&key)[E], int gl, int lane, bool (&head)[E], int (&upto)[E]) {
+    const KEY none = ~static_cast<KEY>(0);
+    const KEY before = __shfl_up(key[E - 1], 1, W);
+    const uint64_t group = W == 64 ? ~0ull : (((1ull << (W & 63)) - 1) << (lane & ~(W - 1)));
+    int n = 0, mine = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const KEY prev = e > 0 ? key[e > 0 ? e - 1 : 0] : before;
+        head[e] = key[e] != none && ((gl == 0 && e == 0) || (key[e] >> B) != (prev >> B));
+        const uint64_t bits = __ballot(head[e]) & group;
+        n += __popcll(bits);
+        mine += __popcll(bits & ((1ull << lane) - 1));   // lanes before this one
     }
-}
-
-__device__ inline int find_pos(const int *arr, int n, int key) {
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (arr[mid] < key) lo = mid + 1;
-        else hi = mid;
-    }
-    return (lo < n && arr[lo] == key) ? lo : -1;
+#pragma unroll
+    for (int e = 0; e < E; ++e) upto[e] = mine += head[e] ? 1 : 0;
+    return n;
 }
 
 // ------------------------------------------------------------ upper bounds
 
+// Rows that one wave takes: at most 64 inner slots and 256 products.
+constexpr int kWaveProducts = 256;
+__device__ inline bool wave_row(int products, int slots) { return products <= kWaveProducts && slots <= kWave; }
+
 // ub[i] = sum of the lengths of Y's rows touched by X's row i (plus the identity's row).
 __global__ __launch_bounds__(256) void k_row_upper_bound(const int *__restrict__ xrowptr, const int *__restrict__ xcol,
                                                         const int *__restrict__ xdiag, const int *__restrict__ yrowptr,
-                                                        int m, int *__restrict__ ub, int small_cap,
-                                                        int *__restrict__ big_list, int *__restrict__ big_count,
+                                                        int m, int *__restrict__ ub, int *__restrict__ big_list,
+                                                        int *__restrict__ big_count,
                                                         int large_cap, int *__restrict__ too_dense) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= m) return;
@@ -120,76 +135,9 @@ __global__ __launch_bounds__(256) void k_row_upper_bound(const int *__restrict__
     if (xdiag) s += yrowptr[xdiag[i] + 1] - yrowptr[xdiag[i]];
     const int v = s > 0x3fffffff ? 0x3fffffff : static_cast<int>(s);
     ub[i] = v;
-    if (v > small_cap) {
+    if (!wave_row(v, xrowptr[i + 1] - xrowptr[i] + (xdiag ? 1 : 0))) {
         if (v > large_cap) atomicMax(too_dense, v);
         big_list[atomicAdd(big_count, 1)] = i;
-    }
-}
-
-// ---------------------------------------------------- SpGEMM symbolic phase
-
-// Insert the keys of row i into an LDS hash table shared by `nthr` threads.
-__device__ inline int insert_row_keys(int i, const int *__restrict__ xrowptr, const int *__restrict__ xcol,
-                                      const int *__restrict__ xdiag, const int *__restrict__ yrowptr,
-                                      const int *__restrict__ ycol, int *table, int mask, int tid, int nthr) {
-    int added = 0;
-    const int q0 = xrowptr[i], q1 = xrowptr[i + 1];
-    const int nk = q1 - q0 + (xdiag ? 1 : 0);
-    for (int q = 0; q < nk; ++q) {
-        const int K = (q < q1 - q0) ? xcol[q0 + q] : xdiag[i];
-        for (int u = yrowptr[K] + tid; u < yrowptr[K + 1]; u += nthr) added += hash_insert(table, mask, ycol[u]) ? 1 : 0;
-    }
-    return added;
-}
-
-// Collect the table's keys, rank-sort them and write them to out[0..n).
-__device__ inline void emit_sorted(const int *table, int slots, int *list, int *list_n, int *out, int tid, int nthr) {
-    for (int s = tid; s < slots; s += nthr) {
-        const int k = table[s];
-        if (k != kEmpty) list[atomicAdd(list_n, 1)] = k;
-    }
-    __syncthreads();
-    const int n = *list_n;
-    for (int a = tid; a < n; a += nthr) {
-        const int k = list[a];
-        int r = 0;
-        for (int b = 0; b < n; ++b) r += (list[b] < k) ? 1 : 0;
-        out[r] = k;
-    }
-}
-
-// Large rows (listed in big_list): one 256-thread workgroup per row, 64 KB hash.
-__global__ __launch_bounds__(256) void k_symbolic_large(const int *__restrict__ xrowptr, const int *__restrict__ xcol,
-                                                       const int *__restrict__ xdiag, const int *__restrict__ yrowptr,
-                                                       const int *__restrict__ ycol, const int *__restrict__ big_list,
-                                                       const int *__restrict__ big_count, int large_cap, int mode,
-                                                       int *__restrict__ cnt, const int *__restrict__ crowptr,
-                                                       int *__restrict__ ccol, const int *__restrict__ ub) {
-    extern __shared__ int lds_i[];
-    int *table = lds_i;                 // kHashLarge
-    int *list = lds_i + kHashLarge;     // kHashLarge / 2
-    __shared__ int nadd;
-    __shared__ int nlist;
-    const int nbig = *big_count;
-    for (int b = blockIdx.x; b < nbig; b += gridDim.x) {
-        const int i = big_list[b];
-        if (ub[i] > large_cap) continue;   // reported as too dense on the host
-        for (int s = threadIdx.x; s < kHashLarge; s += blockDim.x) table[s] = kEmpty;
-        if (threadIdx.x == 0) {
-            nadd = 0;
-            nlist = 0;
-        }
-        __syncthreads();
-        int added = insert_row_keys(i, xrowptr, xcol, xdiag, yrowptr, ycol, table, kHashLarge - 1, threadIdx.x,
-                                    blockDim.x);
-        if (added) atomicAdd(&nadd, added);
-        __syncthreads();
-        if (mode == 0) {
-            if (threadIdx.x == 0) cnt[i] = nadd;
-        } else {
-            emit_sorted(table, kHashLarge, list, &nlist, ccol + crowptr[i], threadIdx.x, blockDim.x);
-        }
-        __syncthreads();
     }
 }
 
@@ -285,50 +233,99 @@ __global__ __launch_bounds__(256) void k_add_values_wave(const int *__restrict__
 
 // ------------------------------------------------- one-point Galerkin merge
 
-// Keys of K's row i: pmap of RA's row columns (>= 0).  Wave per row.
-__global__ __launch_bounds__(256) void k_rap_symbolic(const int *__restrict__ rarp, const int *__restrict__ racol,
-                                                     const int *__restrict__ pmap, int m, int mode,
-                                                     int *__restrict__ cnt, const int *__restrict__ krp,
-                                                     int *__restrict__ kcol, int *__restrict__ too_dense) {
-    __shared__ int tables[4][kHashSmall];
-    __shared__ int lists[4][kHashSmall / 2];
-    __shared__ int counts[4];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int *table = tables[w];
-    for (int i0 = blockIdx.x * 4; i0 < m; i0 += gridDim.x * 4) {
-        const int i = i0 + w;
-        const bool active = i < m && (rarp[i + 1] - rarp[i]) <= kHashSmall / 2;
-        if (i < m && !active && lane == 0) atomicMax(too_dense, rarp[i + 1] - rarp[i]);
-        int slots = kWave;
-        if (active)
-            while (slots < 2 * (rarp[i + 1] - rarp[i])) slots <<= 1;
-        for (int s = lane; s < slots; s += kWave) table[s] = kEmpty;
-        if (lane == 0) counts[w] = 0;
-        wave_sync();   // (every LDS array here is the wave's own)
-        int added = 0;
-        if (active)
-            for (int u = rarp[i] + lane; u < rarp[i + 1]; u += kWave) {
-                const int t = pmap[racol[u]];
-                if (t >= 0) added += hash_insert(table, slots - 1, t) ? 1 : 0;
-            }
-        wave_sync();
-        if (mode == 0) {
+constexpr int kRowBlocks = 1024;   // longest operator row that the merge takes
+
+// A P's pattern: row i's blocks A_it with pmap[t] >= 0, merged by column pmap[t].
+// mode 0: cnt[i] columns and ccnt[i] contributing blocks; mode 1: the sorted
+// columns at kcol + krp[i], each one's blocks (ascending) from kptr in klist
+// (row i's from crow[i]).  One sort of (column, place in the row) by a group of
+// lanes gives all of it.
+struct MergeArgs {
+    const int *rarp, *racol, *pmap;
+    int m;
+    int *cnt, *ccnt;
+    const int *krp;
+    int *kcol;
+    const int *crow;
+    int *kptr, *klist;
+};
+
+constexpr int kMergeBits = 10;
+
+template <int W, int E, int MODE, typename KEY>
+__device__ inline void merge_row(const MergeArgs &M, int i, int lane) {
+    const int gl = lane & (W - 1);
+    const bool active = i < M.m;
+    const int r0 = active ? M.rarp[i] : 0, n = active ? M.rarp[i + 1] - r0 : 0;
+    int col[E];
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) added += __shfl_xor(added, o, kWave);
-            if (active && lane == 0) cnt[i] = added;
-        } else {
-            int *list = lists[w];
-            for (int s = lane; s < slots; s += kWave) {
-                const int k = table[s];
-                if (active && k != kEmpty) list[atomicAdd(&counts[w], 1)] = k;
-            }
-            wave_sync();
-            const int n = active ? counts[w] : 0;
-            int *dst = active ? kcol + krp[i] : nullptr;
-            wave_sort(list, n, kHashSmall / 2, lane);
-            for (int a = lane; a < n; a += kWave) dst[a] = list[a];
+    for (int e = 0; e < E; ++e) col[e] = gl * E + e < n ? M.racol[r0 + gl * E + e] : -1;
+    KEY key[E];
+    int c = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int t = col[e] >= 0 ? M.pmap[col[e]] : -1;
+        key[e] = t >= 0 ? static_cast<KEY>(t) << kMergeBits | static_cast<KEY>(gl * E + e) : ~static_cast<KEY>(0);
+        c += t >= 0 ? 1 : 0;
+    }
+    group_sort<W, E>(key, gl);
+    bool head[E];
+    int upto[E];
+    const int nk = heads<W, E, kMergeBits>(key, gl, lane, head, upto);
+    if (MODE == 0) {
+#pragma unroll
+        for (int o = W / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, kWave);
+        if (active && gl == 0) {
+            M.cnt[i] = nk;
+            M.ccnt[i] = c;
         }
-        wave_sync();
+        return;
+    }
+    const int k0 = active ? M.krp[i] : 0, R0 = active ? M.crow[i] : 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (key[e] == ~static_cast<KEY>(0)) continue;
+        const int at = R0 + gl * E + e;
+        M.klist[at] = r0 + static_cast<int>(key[e] & ((1 << kMergeBits) - 1));
+        if (head[e]) {
+            M.kcol[k0 + upto[e] - 1] = static_cast<int>(key[e] >> kMergeBits);
+            M.kptr[k0 + upto[e] - 1] = at;
+        }
+    }
+}
+
+// A wave takes four consecutive rows at a time, all four, two or one at once as
+// the longest allows.  (rows past 1,024 blocks are reported and left out)
+template <int MODE, typename KEY>
+__global__ __launch_bounds__(256) void k_merge_rows(MergeArgs M, int *__restrict__ too_dense) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (MODE == 1 && blockIdx.x == 0 && threadIdx.x == 0) M.kptr[M.krp[M.m]] = M.crow[M.m];   // end of the last list
+    for (int i0 = (blockIdx.x * 4 + w) * 4; i0 < M.m; i0 += gridDim.x * 16) {
+        const int i = i0 + (lane >> 4);
+        const int n = i < M.m ? M.rarp[i + 1] - M.rarp[i] : 0;
+        int len[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) len[k] = __builtin_amdgcn_readlane(n, 16 * k);
+        if (max(max(len[0], len[1]), max(len[2], len[3])) <= 16) {
+            merge_row<16, 1, MODE, KEY>(M, i, lane);
+            continue;
+        }
+#pragma unroll 1
+        for (int h = 0; h < 4; h += 2) {
+            const int a = h ? len[2] : len[0], b = h ? len[3] : len[1];
+            if (max(a, b) <= 32) {
+                merge_row<32, 1, MODE, KEY>(M, i0 + h + (lane >> 5), lane);
+                continue;
+            }
+#pragma unroll 1
+            for (int k = 0; k < 2; ++k) {
+                const int l = k ? b : a, row = i0 + h + k;
+                if (l <= 64) merge_row<64, 1, MODE, KEY>(M, row, lane);
+                else if (l <= 256) merge_row<64, 4, MODE, KEY>(M, row, lane);
+                else if (l <= kRowBlocks) merge_row<64, 16, MODE, KEY>(M, row, lane);
+                else if (MODE == 0 && lane == 0) atomicMax(too_dense, l);
+            }
+        }
     }
 }
 
@@ -353,250 +350,260 @@ unsigned cap_grid(int64_t g) { return static_cast<unsigned>(g > 65536 * 16 ? 655
 
 namespace {
 
-// Position of the implicit identity column among X's sorted row [q0, q1).
-__device__ inline int identity_slot(const int *__restrict__ xcol, int q0, int q1, int dcol) {
-    int lo = q0, hi = q1;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (xcol[mid] < dcol) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo - q0;
-}
-
-// Exclusive scan of cnt[0..n) in place by the first wave of the workgroup.
-__device__ inline void wave0_scan(int *cnt, int n) {
-    if (threadIdx.x >= 64) return;
-    const int lane = threadIdx.x;
-    int carry = 0;
-    for (int base = 0; base < n; base += 64) {
-        const int v = (base + lane < n) ? cnt[base + lane] : 0;
-        const int x = wave_incl_scan(v);
-        if (base + lane < n) cnt[base + lane] = carry + x - v;
-        carry += __builtin_amdgcn_readlane(x, 63);
-    }
-}
-
-// Contribution lists of one output row: for every output block, the (X block,
-// Y block) pairs that feed it, in ascending inner index (X's sorted row with the
-// identity merged in; the identity is X block -1).  `cols` (LDS) holds the row's
-// sorted output columns, `cnt` (LDS) gets per-block counts, then offsets.
-__device__ inline void row_pairs(int i, const int *__restrict__ xrowptr, const int *__restrict__ xcol,
-                                 const int *__restrict__ xdiag, const int *__restrict__ yrowptr,
-                                 const int *__restrict__ ycol, int c0, int nout, int P0, const int *cols, int *cnt,
-                                 int *__restrict__ pairptr, int2 *__restrict__ pairs) {
-    const int tid = threadIdx.x, nthr = blockDim.x;
-    const int q0 = xrowptr[i], q1 = xrowptr[i + 1];
-    const int nx = q1 - q0;
-    const int dslot = xdiag ? identity_slot(xcol, q0, q1, xdiag[i]) : -1;
-    const int nk = nx + (xdiag ? 1 : 0);
-    for (int qq = 0; qq < nk; ++qq) {
-        const int K = (qq == dslot) ? xdiag[i] : xcol[q0 + qq - ((dslot >= 0 && qq > dslot) ? 1 : 0)];
-        for (int u = yrowptr[K] + tid; u < yrowptr[K + 1]; u += nthr) atomicAdd(&cnt[find_pos(cols, nout, ycol[u])], 1);
-    }
-    __syncthreads();
-    wave0_scan(cnt, nout);
-    __syncthreads();
-    for (int p = tid; p < nout; p += nthr) pairptr[c0 + p] = P0 + cnt[p];
-    __syncthreads();
-    for (int qq = 0; qq < nk; ++qq) {
-        const bool ident = qq == dslot;
-        const int q = ident ? -1 : q0 + qq - ((dslot >= 0 && qq > dslot) ? 1 : 0);
-        const int K = ident ? xdiag[i] : xcol[q];
-        for (int u = yrowptr[K] + tid; u < yrowptr[K + 1]; u += nthr) {
-            const int p = find_pos(cols, nout, ycol[u]);
-            const int pos = cnt[p];     // one writer per block within an inner step
-            cnt[p] = pos + 1;
-            pairs[P0 + pos] = make_int2(q, u);
-        }
-        __syncthreads();
-    }
-}
-
-// Rows listed in big_list: one 256-thread workgroup per row.
-__global__ __launch_bounds__(256) void k_pairs_large(const int *__restrict__ xrowptr, const int *__restrict__ xcol,
-                                                    const int *__restrict__ xdiag, const int *__restrict__ yrowptr,
-                                                    const int *__restrict__ ycol, const int *__restrict__ big_list,
-                                                    const int *__restrict__ big_count, const int *__restrict__ crowptr,
-                                                    const int *__restrict__ ccol, const int *__restrict__ prow,
-                                                    int *__restrict__ pairptr, int2 *__restrict__ pairs) {
-    __shared__ int cols[kHashLarge / 2];
-    __shared__ int cnt[kHashLarge / 2];
-    const int nbig = *big_count;
-    for (int bi = blockIdx.x; bi < nbig; bi += gridDim.x) {
-        const int i = big_list[bi];
-        const int c0 = crowptr[i], nout = crowptr[i + 1] - c0;
-        for (int p = threadIdx.x; p < nout; p += blockDim.x) {
-            cols[p] = ccol[c0 + p];
-            cnt[p] = 0;
-        }
-        __syncthreads();
-        row_pairs(i, xrowptr, xcol, xdiag, yrowptr, ycol, c0, nout, prow[i], cols, cnt, pairptr, pairs);
-        __syncthreads();
-    }
-}
-
-// Intra-wave ordering of LDS traffic (the rows of k_symbolic_flat are per
-// wave and take different numbers of steps, so no workgroup barrier fits).
-// Up to 64 inner slots of output row i, one per lane: slot base + lane of the
-// row's sorted inner indices (X's row with its implicit identity block merged
-// in at its column).  A lane holds its slot's X block (-1: the identity), the
-// first Y block of the slot's Y row and the row's length, and the number of
-// products of the chunk's slots before its own; `total` is the chunk's count.
-struct SlotChunk {
-    int q, ybeg, len, excl, total;
+// Symbolic product C = X Y (X with an implicit identity block at column xdiag[i]
+// merged into its row i).  A row's products are numbered flat, ascending inner
+// index first; sorting (output column, number) gives the row's columns in order and
+// each output block's pair list in ascending inner index (a Y row feeds a block at
+// most once).  mode 0: cnt[i] columns; mode 1: columns at ccol + crowptr[i], pairs at
+// prow[i] ..., block t's from pairptr[t].
+struct SymArgs {
+    const int *xrowptr, *xcol, *xdiag, *yrowptr, *ycol;
+    int m;
+    const int *ub;
+    int *cnt;
+    const int *crowptr;
+    int *ccol;
+    const int *prow;
+    int *pairptr;
+    int2 *pairs;
 };
 
-__device__ inline SlotChunk load_slots(int base, int nk, int q0, int dslot, int dcol, const int *__restrict__ xcol,
-                                       const int *__restrict__ yrowptr, int lane) {
-    SlotChunk c{-1, 0, 0, 0, 0};
-    const int qq = base + lane;
-    if (qq < nk) {
-        const bool ident = qq == dslot;
-        c.q = ident ? -1 : q0 + qq - ((dslot >= 0 && qq > dslot) ? 1 : 0);
-        const int K = ident ? dcol : xcol[c.q];
-        c.ybeg = yrowptr[K];
-        c.len = yrowptr[K + 1] - c.ybeg;
+constexpr int kPairBits = 10;   // (up to 1,024 products a wave)
+
+// One row per group of W lanes, E products per lane: one inner slot per lane, then
+// product p's slot by binary search over the lanes' offsets.
+template <int W, int E, int MODE, typename KEY>
+__device__ inline void product_row(const SymArgs &S, int i, int lane) {
+    const int gl = lane & (W - 1);
+    const bool active = i < S.m;
+    int q0 = 0, nx = 0, dcol = 0;
+    if (active) {
+        q0 = S.xrowptr[i];
+        nx = S.xrowptr[i + 1] - q0;
+        if (S.xdiag) dcol = S.xdiag[i];
     }
-    const int x = wave_incl_scan(c.len);
-    c.excl = x - c.len;
-    c.total = __builtin_amdgcn_readlane(x, 63);
-    return c;
+    int K = gl < nx ? S.xcol[q0 + gl] : INT_MAX, q = q0 + gl;
+    bool slot = gl < nx;
+    if (S.xdiag) {   // the identity takes its place, the slots from there on move up by one
+        const uint64_t group = W == 64 ? ~0ull : (((1ull << (W & 63)) - 1) << (lane & ~(W - 1)));
+        const int dslot = __popcll(__ballot(slot && K < dcol) & group);
+        const int Kp = __shfl_up(K, 1, W);
+        if (gl > dslot) {
+            K = Kp;
+            --q;
+        } else if (gl == dslot) {
+            K = dcol;
+            q = -1;
+        }
+        slot = active && gl <= nx;
+    }
+    int ybeg = 0, len = 0;
+    if (slot) {
+        ybeg = S.yrowptr[K];
+        len = S.yrowptr[K + 1] - ybeg;
+    }
+    int excl = len;
+#pragma unroll
+    for (int d = 1; d < W; d <<= 1) {
+        const int y = __shfl_up(excl, d, W);
+        excl += gl >= d ? y : 0;
+    }
+    const int total = __shfl(excl, W - 1, W);
+    excl -= len;
+    auto slot_of = [&](int p) {   // the last slot that starts at or before p (empty slots lie before their successor)
+        int j = 0;
+#pragma unroll
+        for (int step = W / 2; step > 0; step >>= 1) j += __shfl(excl, j + step, W) <= p ? step : 0;
+        return j;
+    };
+    KEY key[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int p = gl * E + e, j = slot_of(p);
+        const int u = __shfl(ybeg, j, W) + p - __shfl(excl, j, W);
+        key[e] = p < total ? static_cast<KEY>(S.ycol[u]) << kPairBits | static_cast<KEY>(p) : ~static_cast<KEY>(0);
+    }
+    group_sort<W, E>(key, gl);
+    bool head[E];
+    int upto[E];
+    const int n = heads<W, E, kPairBits>(key, gl, lane, head, upto);
+    if (MODE == 0) {
+        if (active && gl == 0) S.cnt[i] = n;
+        return;
+    }
+    const int c0 = active ? S.crowptr[i] : 0, P0 = active ? S.prow[i] : 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int p = static_cast<int>(key[e] & ((1 << kPairBits) - 1)), j = slot_of(p);
+        const int fq = __shfl(q, j, W), fu = __shfl(ybeg, j, W) + p - __shfl(excl, j, W);
+        if (key[e] == ~static_cast<KEY>(0)) continue;
+        const int at = P0 + gl * E + e;
+        S.pairs[at] = make_int2(fq, fu);
+        if (head[e]) {
+            S.ccol[c0 + upto[e] - 1] = static_cast<int>(key[e] >> kPairBits);
+            S.pairptr[c0 + upto[e] - 1] = at;
+        }
+    }
 }
 
-// Product p < c.total of a chunk: the slot j holding it (the last lane whose
-// excl <= p; empty slots share their successor's excl and lie before it) and
-// its (X block, Y block) pair.  Every lane of the wave must call it (it reads
-// other lanes' registers); p >= c.total gives a pair of no meaning.
-__device__ inline int2 locate(const SlotChunk &c, int p) {
-    int j = 0;
+// A wave takes four consecutive rows at a time: all four at once in 16 lanes each,
+// two in 32, or one after the other, as the longest needs (products and inner
+// slots); rows of more than kWaveProducts products or kWave slots are left to
+// k_product_large.  Bound by the row's chain of loads (row range, inner columns,
+// their rows, their columns) and the sort's about 60 to 500 lane moves.  One row per
+// wave with LDS hash tables, per-block counts and 64-step ranks took 40 ms of the
+// setup of 64 Q2 transport operators (2.0 M rows; products, merges and their lists
+// together), this takes 8.
+template <int MODE, typename KEY>
+__global__ __launch_bounds__(256) void k_product_rows(SymArgs S) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (MODE == 1 && blockIdx.x == 0 && threadIdx.x == 0) S.pairptr[S.crowptr[S.m]] = S.prow[S.m];   // last list's end
+    for (int i0 = (blockIdx.x * 4 + w) * 4; i0 < S.m; i0 += gridDim.x * 16) {
+        const int i = i0 + (lane >> 4);
+        int n = 0;
+        if (i < S.m) {
+            const int slots = S.xrowptr[i + 1] - S.xrowptr[i] + (S.xdiag ? 1 : 0), products = S.ub[i];
+            n = wave_row(products, slots) ? max(products, slots) : INT_MAX;
+        }
+        int len[4];
 #pragma unroll
-    for (int step = 32; step > 0; step >>= 1) {
-        const int e = __shfl(c.excl, j + step, 64);
-        if (e <= p) j += step;
+        for (int k = 0; k < 4; ++k) len[k] = __builtin_amdgcn_readlane(n, 16 * k);
+        if (max(max(len[0], len[1]), max(len[2], len[3])) <= 16) {
+            product_row<16, 1, MODE, KEY>(S, i, lane);
+            continue;
+        }
+#pragma unroll 1
+        for (int h = 0; h < 4; h += 2) {
+            const int a = h ? len[2] : len[0], b = h ? len[3] : len[1];
+            if (max(a, b) <= 32) {
+                product_row<32, 1, MODE, KEY>(S, i0 + h + (lane >> 5), lane);
+                continue;
+            }
+#pragma unroll 1
+            for (int k = 0; k < 2; ++k) {
+                const int l = k ? b : a, row = i0 + h + k;
+                if (l <= 64) product_row<64, 1, MODE, KEY>(S, row, lane);
+                else if (l <= 128) product_row<64, 2, MODE, KEY>(S, row, lane);
+                else if (l <= kWaveProducts) product_row<64, 4, MODE, KEY>(S, row, lane);
+            }
+        }
     }
-    const int q = __shfl(c.q, j, 64);
-    const int u = __shfl(c.ybeg, j, 64) + (p - __shfl(c.excl, j, 64));
-    return make_int2(q, u);
 }
 
-// Rows with ub <= small cap, one wave per row (4 per workgroup): every product
-// of the row is enumerated flat across the wave's lanes (a chunk of up to 64
-// inner slots at a time), so the row's loads do not queue behind one another
-// slot by slot.  mode 0: cnt[i] = the row's distinct output columns.  mode 1:
-// the sorted columns at ccol + crowptr[i], and each output block's pair list
-// (pairs at prow[i] ..., block t's from pairptr[t]) in ascending inner index:
-// products are counted per block, the counts scanned, and then placed in flat
-// order 64 at a time, each lane after the lanes before it in the same step
-// that feed the same block (a Y row feeds a block at most once).
-__global__ __launch_bounds__(256) void k_symbolic_flat(const int *__restrict__ xrowptr, const int *__restrict__ xcol,
-                                                      const int *__restrict__ xdiag, const int *__restrict__ yrowptr,
-                                                      const int *__restrict__ ycol, int m, const int *__restrict__ ub,
-                                                      int small_cap, int mode, int *__restrict__ cnt,
-                                                      const int *__restrict__ crowptr, int *__restrict__ ccol,
-                                                      const int *__restrict__ prow, int *__restrict__ pairptr,
-                                                      int2 *__restrict__ pairs) {
-    __shared__ int tables[4][kHashSmall];
-    __shared__ int lists[4][kHashSmall / 2];
-    __shared__ int counts[4];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int *table = tables[w];
-    int *list = lists[w];
-    if (mode == 1 && blockIdx.x == 0 && threadIdx.x == 0) pairptr[crowptr[m]] = prow[m];   // end of the last list
-    for (int i0 = blockIdx.x * 4; i0 < m; i0 += gridDim.x * 4) {
-        const int i = i0 + w;
-        const bool active = i < m && ub[i] <= small_cap;
-        // table of the next power of two >= 2 ub slots (at least one per lane)
-        int slots = kWave;
-        if (active)
-            while (slots < 2 * ub[i]) slots <<= 1;
-        for (int t = lane; t < slots; t += kWave) table[t] = kEmpty;
-        if (lane == 0) counts[w] = 0;
-        wave_sync();   // (every LDS array here is the wave's own)
-        int q0 = 0, nk = 0, dslot = -1, dcol = 0;
-        if (active) {
-            q0 = xrowptr[i];
-            const int q1 = xrowptr[i + 1];
-            nk = q1 - q0;
-            if (xdiag) {
-                dcol = xdiag[i];
-                dslot = identity_slot(xcol, q0, q1, dcol);
-                ++nk;
-            }
-        }
-        int added = 0;
-        for (int base = 0; base < nk; base += kWave) {
-            const SlotChunk c = load_slots(base, nk, q0, dslot, dcol, xcol, yrowptr, lane);
-            for (int r0 = 0; r0 < c.total; r0 += kWave) {
-                const int p = r0 + lane;
-                const int2 pr = locate(c, p);
-                if (p < c.total) added += hash_insert(table, slots - 1, ycol[pr.y]) ? 1 : 0;
-            }
-        }
-        wave_sync();
-        if (mode == 0) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) added += __shfl_xor(added, o, kWave);
-            if (active && lane == 0) cnt[i] = added;
-        } else {
-            for (int t = lane; t < slots; t += kWave) {
-                const int k = table[t];
-                if (active && k != kEmpty) list[atomicAdd(&counts[w], 1)] = k;
-            }
-            wave_sync();
-            const int n = active ? counts[w] : 0;
-            // the sorted columns go to ccol and to the table's first n slots
-            int *sorted = table;
-            int *off = table + kHashSmall / 2;
-            const int c0 = active ? crowptr[i] : 0;
-            wave_sort(list, n, kHashSmall / 2, lane);
-            for (int a = lane; a < n; a += kWave) {
-                sorted[a] = list[a];
-                ccol[c0 + a] = list[a];
-            }
-            for (int a = lane; a < n; a += kWave) off[a] = 0;
-            wave_sync();
-            // products per output block, then their offsets
-            for (int base = 0; base < nk; base += kWave) {
-                const SlotChunk c = load_slots(base, nk, q0, dslot, dcol, xcol, yrowptr, lane);
-                for (int r0 = 0; r0 < c.total; r0 += kWave) {
-                    const int p = r0 + lane;
-                    const int2 pr = locate(c, p);
-                    if (p < c.total) atomicAdd(&off[find_pos(sorted, n, ycol[pr.y])], 1);
+// The rows in big_list: up to 1,024 products and 64 slots a wave each, up to
+// kLargeProducts products the workgroup together, keys and pairs in LDS (rows past
+// the limit are reported on the host).
+constexpr int kLargeProducts = 4096;
+constexpr int kLargeBits = 12;
+constexpr int kLargeGrid = 512;
+
+template <int MODE, typename KEY>
+__global__ __launch_bounds__(256) void k_product_large(SymArgs S, const int *__restrict__ big_list,
+                                                      const int *__restrict__ big_count) {
+    extern __shared__ uint64_t lkey[];                             // [kLargeProducts]
+    int2 *pay = reinterpret_cast<int2 *>(lkey + kLargeProducts);   // [kLargeProducts], mode 1
+    __shared__ int sq[256], sy[256], se[256], wsum[4];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto block_excl = [&](int v, int &total) {   // exclusive scan over the workgroup
+        const int x = wave_incl_scan(v);
+        __syncthreads();
+        if (lane == 63) wsum[w] = x;
+        __syncthreads();
+        int before = 0;
+        for (int k = 0; k < w; ++k) before += wsum[k];
+        total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        return before + x - v;
+    };
+    const int nbig = *big_count;
+    auto kind = [&](int b) {   // of list entry b: 0 a wave's 512 products, 1 its 1,024, 2 the workgroup's, 3 none
+        if (b >= nbig) return 3;
+        const int i = big_list[b], products = S.ub[i];
+        const int slots = S.xrowptr[i + 1] - S.xrowptr[i] + (S.xdiag ? 1 : 0);
+        return products > kLargeProducts ? 3 : (products > 1024 || slots > kWave ? 2 : (products > 512 ? 1 : 0));
+    };
+    for (int b0 = blockIdx.x * 4; b0 < nbig; b0 += gridDim.x * 4) {
+        const int mine = __builtin_amdgcn_readfirstlane(kind(b0 + w));
+        if (mine == 0) product_row<64, 8, MODE, KEY>(S, big_list[b0 + w], lane);
+        else if (mine == 1) product_row<64, 16, MODE, KEY>(S, big_list[b0 + w], lane);
+        for (int b = b0; b < b0 + 4; ++b) {
+            if (kind(b) != 2) continue;   // (the same in every thread)
+            const int i = big_list[b];
+            const int q0 = S.xrowptr[i], nx = S.xrowptr[i + 1] - q0;
+            int dslot = INT_MAX, dcol = 0;
+            if (S.xdiag) {
+                dcol = S.xdiag[i];
+                int lo = 0, hi = nx;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (S.xcol[q0 + mid] < dcol) lo = mid + 1;
+                    else hi = mid;
                 }
+                dslot = lo;
             }
-            wave_sync();
-            int carry = 0;
-            for (int base = 0; base < n; base += kWave) {
-                const int v = base + lane < n ? off[base + lane] : 0;
-                const int x = wave_incl_scan(v);
-                if (base + lane < n) off[base + lane] = carry + x - v;
-                carry += __builtin_amdgcn_readlane(x, 63);
+            const int nk = nx + (S.xdiag ? 1 : 0);
+            int flat = 0;   // products of the slots before this chunk
+            for (int base = 0; base < nk; base += 256) {
+                const int qq = base + tid;
+                int q = -1, ybeg = 0, len = 0;
+                if (qq < nk) {
+                    if (qq != dslot) q = q0 + qq - (qq > dslot ? 1 : 0);
+                    const int K = q < 0 ? dcol : S.xcol[q];
+                    ybeg = S.yrowptr[K];
+                    len = S.yrowptr[K + 1] - ybeg;
+                }
+                int total;
+                const int excl = block_excl(len, total);
+                sq[tid] = q;
+                sy[tid] = ybeg;
+                se[tid] = excl;
+                __syncthreads();
+                for (int p = tid; p < total; p += 256) {
+                    int j = 0;
+    #pragma unroll
+                    for (int step = 128; step > 0; step >>= 1) j += se[j + step] <= p ? step : 0;
+                    const int u = sy[j] + p - se[j];
+                    lkey[flat + p] = static_cast<uint64_t>(S.ycol[u]) << kLargeBits | static_cast<uint64_t>(flat + p);
+                    if (MODE == 1) pay[flat + p] = make_int2(sq[j], u);
+                }
+                flat += total;
+                __syncthreads();
             }
-            wave_sync();
-            const int P0 = active ? prow[i] : 0;
-            for (int a = lane; a < n; a += kWave) pairptr[c0 + a] = P0 + off[a];
-            wave_sync();
-            for (int base = 0; base < nk; base += kWave) {
-                const SlotChunk c = load_slots(base, nk, q0, dslot, dcol, xcol, yrowptr, lane);
-                for (int r0 = 0; r0 < c.total; r0 += kWave) {
-                    const int p = r0 + lane;
-                    int pos = -1;
-                    const int2 pr = locate(c, p);
-                    if (p < c.total) pos = find_pos(sorted, n, ycol[pr.y]);
-                    int rank = 0;
-                    for (int l = 0; l < kWave; ++l) {
-                        const int pl = __builtin_amdgcn_readlane(pos, l);   // (l is the same in every lane)
-                        rank += (l < lane && pl == pos) ? 1 : 0;
+            int N = 256;
+            while (N < flat) N <<= 1;
+            for (int t = flat + tid; t < N; t += 256) lkey[t] = ~0ull;
+            __syncthreads();
+            for (int k = 2; k <= N; k <<= 1)
+                for (int j = k >> 1; j > 0; j >>= 1) {
+                    for (int t = tid; t < N / 2; t += 256) {
+                        const int x = 2 * t - (t & (j - 1)), y = x + j;
+                        const uint64_t a = lkey[x], c = lkey[y];
+                        if (((x & k) == 0) == (c < a)) {
+                            lkey[x] = c;
+                            lkey[y] = a;
+                        }
                     }
-                    if (pos >= 0) pairs[P0 + off[pos] + rank] = pr;
-                    wave_sync();
-                    if (pos >= 0) atomicAdd(&off[pos], 1);
-                    wave_sync();
+                    __syncthreads();
                 }
+            const int per = N / 256, t0 = tid * per;
+            int n = 0;
+            for (int t = t0; t < t0 + per && t < flat; ++t)
+                n += (t == 0 || (lkey[t] >> kLargeBits) != (lkey[t - 1] >> kLargeBits)) ? 1 : 0;
+            int total;
+            int at = block_excl(n, total);
+            if (MODE == 0) {
+                if (tid == 0) S.cnt[i] = total;
+            } else {
+                const int c0 = S.crowptr[i], P0 = S.prow[i];
+                for (int t = t0; t < t0 + per && t < flat; ++t)
+                    if (t == 0 || (lkey[t] >> kLargeBits) != (lkey[t - 1] >> kLargeBits)) {
+                        S.ccol[c0 + at] = static_cast<int>(lkey[t] >> kLargeBits);
+                        S.pairptr[c0 + at] = P0 + t;
+                        ++at;
+                    }
+                for (int t = tid; t < flat; t += 256) S.pairs[P0 + t] = pay[lkey[t] & (kLargeProducts - 1)];
             }
+            __syncthreads();
         }
-        wave_sync();
     }
 }
 
@@ -848,64 +855,7 @@ __global__ __launch_bounds__(256) void k_gather_mask(int64_t n, const uint32_t *
     if (t < n && t < *count) out[t] = in[src[t]];
 }
 
-// ---------------------------------------------------- Galerkin merge lists
-
-__global__ __launch_bounds__(256) void k_rap_count_contrib(const int *__restrict__ rarp, const int *__restrict__ racol,
-                                                          const int *__restrict__ pmap, int m, int *__restrict__ cnt) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    int c = 0;
-    for (int u = rarp[i]; u < rarp[i + 1]; ++u) c += (pmap[racol[u]] >= 0) ? 1 : 0;
-    cnt[i] = c;
-}
-
-// For K's row i: the RA blocks of row i merged into each K block, in ascending
-// RA column.  One 64-thread workgroup per row (rows have <= 1024 RA blocks).
-__global__ __launch_bounds__(64) void k_rap_contrib(const int *__restrict__ rarp, const int *__restrict__ racol,
-                                                   const int *__restrict__ pmap, int m, const int *__restrict__ krp,
-                                                   const int *__restrict__ kcol, const int *__restrict__ crow,
-                                                   int *__restrict__ kptr, int *__restrict__ klist) {
-    __shared__ int kc[kHashSmall / 2];
-    __shared__ int off[kHashSmall / 2];
-    const int lane = threadIdx.x;
-    if (blockIdx.x == 0 && lane == 0) kptr[krp[m]] = crow[m];   // the end of the last block's list
-    for (int i = blockIdx.x; i < m; i += gridDim.x) {
-        const int r0 = rarp[i], nra = rarp[i + 1] - r0;
-        const int k0 = krp[i], nk = krp[i + 1] - k0;
-        const int R0 = crow[i];
-        for (int p = lane; p < nk; p += 64) {
-            kc[p] = kcol[k0 + p];
-            off[p] = 0;
-        }
-        __syncthreads();
-        for (int u = lane; u < nra; u += 64) {
-            const int t = pmap[racol[r0 + u]];
-            if (t >= 0) atomicAdd(&off[find_pos(kc, nk, t)], 1);
-        }
-        __syncthreads();
-        wave0_scan(off, nk);
-        __syncthreads();
-        for (int p = lane; p < nk; p += 64) kptr[k0 + p] = R0 + off[p];
-        __syncthreads();
-        for (int u0 = 0; u0 < nra; u0 += 64) {
-            const int u = u0 + lane;
-            int p = -1;
-            if (u < nra) {
-                const int t = pmap[racol[r0 + u]];
-                if (t >= 0) p = find_pos(kc, nk, t);
-            }
-            int rank = 0;
-            for (int l = 0; l < 64; ++l) {
-                const int pl = __builtin_amdgcn_readlane(p, l);   // (l is the same in every lane)
-                rank += (l < lane && pl == p) ? 1 : 0;
-            }
-            if (p >= 0) klist[R0 + off[p] + rank] = r0 + u;
-            __syncthreads();
-            if (p >= 0) atomicAdd(&off[p], 1);
-            __syncthreads();
-        }
-    }
-}
+// --------------------------------------------------- Galerkin merged values
 
 __global__ __launch_bounds__(256) void k_rap_values(int64_t nnz, int bb, const int *__restrict__ kptr,
                                                    const int *__restrict__ klist, const double *__restrict__ RA,
@@ -1101,23 +1051,23 @@ void spgemm_structure(const DevBSR &X, const int *xdiag, const DevBSR &Y, DevBSR
         C.colidx.alloc(0);
         return;
     }
-    const int small_cap = kHashSmall / 2, large_cap = kHashLarge / 2;
     // flags: big-row count, too-dense row, then the scans' totals (nnz, pairs), read in one copy
     DBuf<int> ub(m), cnt(m), big_list(m), flags(4), prow(static_cast<size_t>(m) + 1);
     NAIR_HIP(hipMemsetAsync(flags.get(), 0, sizeof(int) * 2, s));
-    int *big_count = flags.get(), *too_dense = flags.get() + 1;
+    int *big_count = flags.get();
     k_row_upper_bound<<<grid_for(m, 256), 256, 0, s>>>(X.rowptr.get(), X.colidx.get(), xdiag, Y.rowptr.get(), m,
-                                                      ub.get(), small_cap, big_list.get(), big_count, large_cap,
-                                                      too_dense);
-    const unsigned gs = cap_grid((m + 3) / 4);
-    const size_t lds_large = sizeof(int) * (kHashLarge + kHashLarge / 2);
-    k_symbolic_flat<<<gs, 256, 0, s>>>(X.rowptr.get(), X.colidx.get(), xdiag, Y.rowptr.get(), Y.colidx.get(), m,
-                                       ub.get(), small_cap, 0, cnt.get(), nullptr, nullptr, nullptr, nullptr, nullptr);
+                                                      ub.get(), big_list.get(), big_count, kLargeProducts,
+                                                      flags.get() + 1);
+    SymArgs S{X.rowptr.get(), X.colidx.get(), xdiag, Y.rowptr.get(), Y.colidx.get(), m, ub.get(), cnt.get()};
+    const unsigned gs = cap_grid((m + 15) / 16);
+    const bool narrow = Y.ncols < (1 << (32 - kPairBits));   // (column, product) fit 32 bits, no key all ones
+    if (narrow) k_product_rows<0, uint32_t><<<gs, 256, 0, s>>>(S);
+    else k_product_rows<0, uint64_t><<<gs, 256, 0, s>>>(S);
     {
         TimerScope ts(TK_SPGEMM_SYM, g_timer_level, s);
-        k_symbolic_large<<<256, 256, lds_large, s>>>(X.rowptr.get(), X.colidx.get(), xdiag, Y.rowptr.get(),
-                                                     Y.colidx.get(), big_list.get(), big_count, large_cap, 0,
-                                                     cnt.get(), nullptr, nullptr, ub.get());
+        constexpr size_t lds = sizeof(uint64_t) * kLargeProducts;
+        if (narrow) k_product_large<0, uint32_t><<<kLargeGrid, 256, lds, s>>>(S, big_list.get(), big_count);
+        else k_product_large<0, uint64_t><<<kLargeGrid, 256, lds, s>>>(S, big_list.get(), big_count);
     }
     NAIR_HIP(hipGetLastError());
     scan_exclusive2(cnt.get(), C.rowptr.get(), m, flags.get() + 2, ub.get(), prow.get(), m, flags.get() + 3, s);
@@ -1126,24 +1076,27 @@ void spgemm_structure(const DevBSR &X, const int *xdiag, const DevBSR &Y, DevBSR
     const int nnz = hflags[2], npairs = hflags[3];
     if (hflags[1] > 0)
         fail(NAIR_ENOMEM, "sparse product row has " + std::to_string(hflags[1]) + " candidate blocks (limit " +
-                              std::to_string(large_cap) + ")");
+                              std::to_string(kLargeProducts) + ")");
     C.nnzb = nnz;
     C.colidx.alloc(nnz);
     if (nnz == 0) return;
     P.pairptr.alloc(static_cast<size_t>(nnz) + 1);
     P.pairs.alloc(npairs);
     P.n = npairs;
-    k_symbolic_flat<<<gs, 256, 0, s>>>(X.rowptr.get(), X.colidx.get(), xdiag, Y.rowptr.get(), Y.colidx.get(), m,
-                                       ub.get(), small_cap, 1, nullptr, C.rowptr.get(), C.colidx.get(), prow.get(),
-                                       P.pairptr.get(), P.pairs.get());
-    if (hflags[0] > 0)
-        k_symbolic_large<<<256, 256, lds_large, s>>>(X.rowptr.get(), X.colidx.get(), xdiag, Y.rowptr.get(),
-                                                     Y.colidx.get(), big_list.get(), big_count, large_cap, 1, nullptr,
-                                                     C.rowptr.get(), C.colidx.get(), ub.get());
-    if (hflags[0] > 0)
-        k_pairs_large<<<256, 256, 0, s>>>(X.rowptr.get(), X.colidx.get(), xdiag, Y.rowptr.get(), Y.colidx.get(),
-                                          big_list.get(), big_count, C.rowptr.get(), C.colidx.get(), prow.get(),
-                                          P.pairptr.get(), P.pairs.get());
+    S.crowptr = C.rowptr.get();
+    S.ccol = C.colidx.get();
+    S.prow = prow.get();
+    S.pairptr = P.pairptr.get();
+    S.pairs = P.pairs.get();
+    if (narrow) k_product_rows<1, uint32_t><<<gs, 256, 0, s>>>(S);
+    else k_product_rows<1, uint64_t><<<gs, 256, 0, s>>>(S);
+    if (hflags[0] > 0) {
+        constexpr size_t lds = (sizeof(uint64_t) + sizeof(int2)) * kLargeProducts;
+        auto kern = narrow ? k_product_large<1, uint32_t> : k_product_large<1, uint64_t>;
+        NAIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+        kern<<<kLargeGrid, 256, lds, s>>>(S, big_list.get(), big_count);
+    }
     NAIR_HIP(hipGetLastError());
 }
 
@@ -1235,10 +1188,11 @@ void merge_columns(const DevBSR &A, const int *pmap, int nc, DevBSR &Z, DevBSR &
     DBuf<int> cnt(m), ccnt(m), crow(static_cast<size_t>(m) + 1), flags(3);
     AP.rowptr.alloc(static_cast<size_t>(m) + 1);
     NAIR_HIP(hipMemsetAsync(flags.get(), 0, sizeof(int), s));
-    const unsigned gs = cap_grid((m + 3) / 4);
-    k_rap_symbolic<<<gs, 256, 0, s>>>(A.rowptr.get(), A.colidx.get(), pmap, m, 0, cnt.get(), nullptr, nullptr,
-                                      flags.get());
-    k_rap_count_contrib<<<grid_for(m, 256), 256, 0, s>>>(A.rowptr.get(), A.colidx.get(), pmap, m, ccnt.get());
+    const unsigned gs = cap_grid((m + 15) / 16);
+    MergeArgs M{A.rowptr.get(), A.colidx.get(), pmap, m, cnt.get(), ccnt.get()};
+    const bool narrow = nc < (1 << (32 - kMergeBits));   // (column, place) fit 32 bits, no key all ones
+    if (narrow) k_merge_rows<0, uint32_t><<<gs, 256, 0, s>>>(M, flags.get());
+    else k_merge_rows<0, uint64_t><<<gs, 256, 0, s>>>(M, flags.get());
     NAIR_HIP(hipGetLastError());
     scan_exclusive2(cnt.get(), AP.rowptr.get(), m, flags.get() + 1, ccnt.get(), crow.get(), m, flags.get() + 2, s);
     int hflags[3] = {0, 0, 0};
@@ -1250,17 +1204,20 @@ void merge_columns(const DevBSR &A, const int *pmap, int nc, DevBSR &Z, DevBSR &
     if (zdev) Z.nnzb = zcount;
     if (hflags[0] > 0)
         fail(NAIR_ENOMEM, "operator row has " + std::to_string(hflags[0]) + " blocks (limit " +
-                              std::to_string(kHashSmall / 2) + ")");
+                              std::to_string(kRowBlocks) + ")");
     const int nnz = hflags[1], ncontrib = hflags[2];
     AP.nnzb = nnz;
     AP.colidx.alloc(static_cast<size_t>(nnz));
     if (!ymap) AP.vals.alloc(static_cast<size_t>(nnz) * bb);
     if (nnz == 0) return;
     DBuf<int> kptr(static_cast<size_t>(nnz) + 1), klist(static_cast<size_t>(ncontrib));
-    k_rap_symbolic<<<gs, 256, 0, s>>>(A.rowptr.get(), A.colidx.get(), pmap, m, 1, nullptr, AP.rowptr.get(),
-                                      AP.colidx.get(), flags.get());
-    k_rap_contrib<<<cap_grid(m), 64, 0, s>>>(A.rowptr.get(), A.colidx.get(), pmap, m, AP.rowptr.get(),
-                                             AP.colidx.get(), crow.get(), kptr.get(), klist.get());
+    M.krp = AP.rowptr.get();
+    M.kcol = AP.colidx.get();
+    M.crow = crow.get();
+    M.kptr = kptr.get();
+    M.klist = klist.get();
+    if (narrow) k_merge_rows<1, uint32_t><<<gs, 256, 0, s>>>(M, flags.get());
+    else k_merge_rows<1, uint64_t><<<gs, 256, 0, s>>>(M, flags.get());
     if (ymap) {
         DBuf<int> flag(static_cast<size_t>(nnz)), midx(static_cast<size_t>(nnz) + 1);
         k_ap_flags<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, kptr.get(), flag.get());
