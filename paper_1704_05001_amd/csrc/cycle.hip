@@ -919,6 +919,86 @@ __global__ __launch_bounds__(kThreads) void k_restrict(const int *__restrict__ z
     if (act && L.g == 0) rc[static_cast<int64_t>(i) * bs + L.a] = static_cast<VT>(rv + acc);
 }
 
+// Products of the stored rows v0 <= v < v1 with their columns' blocks of x, one
+// lane per row, into dot[v - v0]: row v's values at vals + at(v) BS, its column in
+// qcol[v - v0] (NEG: negative means no product; its loads go to block 0, since loads
+// under a condition would wait for qcol).  A 9 x 9 FP64 lane takes two rows at a
+// time, their loads before either product: 8% faster at Q2 N = 256; in FP32, and with
+// longer rows, the registers cost more than that gives.  PIN: the whole 25 x 25 FP64
+// row is loaded before its product, at three waves per SIMD: left to itself the
+// compiler keeps to more waves and waits for x's words one load at a time (103 us a
+// restriction at Q4 N = 512, against 82).  Where the caller's own registers are few
+// (the later sweeps, 29.5 us against 32) it does better alone.
+template <int BS, bool NEG, bool PIN, typename MT, typename VT, typename AT>
+__device__ inline void stored_row_dots(const MT *__restrict__ vals, const VT *__restrict__ x, const int *qcol,
+                                       double *dot, int v0, int v1, int bs, AT &&at) {
+    constexpr int U = BS > 0 && BS <= 9 && sizeof(MT) == 8 ? 2 : 1;
+    if constexpr (U == 1) {
+        for (int v = v0 + static_cast<int>(threadIdx.x); v < v1; v += kThreads) {
+            const int J = qcol[v - v0];
+            const MT *blk = vals + at(v) * bs;
+            const VT *xj = x + static_cast<int64_t>(NEG ? max(J, 0) : J) * bs;
+            double d;
+            if constexpr (BS >= 25 && sizeof(MT) == 8 && PIN) {   // (every load before the first product)
+                MT a[BS];
+                VT b[BS];
+#pragma unroll
+                for (int c = 0; c < BS; ++c) a[c] = blk[c];
+#pragma unroll
+                for (int c = 0; c < BS; ++c) b[c] = xj[c];
+                __builtin_amdgcn_sched_barrier(0);
+                d = block_row_dot<BS>(a, b, BS);
+            } else {
+                d = block_row_dot<BS>(blk, xj, bs);
+            }
+            dot[v - v0] = !NEG || J >= 0 ? d : 0.0;
+        }
+    } else {
+        for (int v = v0 + static_cast<int>(threadIdx.x); v < v1; v += U * kThreads) {
+            MT a[U][BS];
+            VT b[U][BS];
+            int J[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {   // (past the end: the last row again)
+                const int vu = min(v + u * kThreads, v1 - 1);
+                J[u] = qcol[vu - v0];
+                const MT *blk = vals + at(vu) * BS;
+                const VT *xj = x + static_cast<int64_t>(NEG ? max(J[u], 0) : J[u]) * BS;
+#pragma unroll
+                for (int c = 0; c < BS; ++c) a[u][c] = blk[c];
+#pragma unroll
+                for (int c = 0; c < BS; ++c) b[u][c] = xj[c];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (v + u * kThreads < v1)
+                    dot[v + u * kThreads - v0] = !NEG || J[u] >= 0 ? block_row_dot<BS>(a[u], b[u], BS) : 0.0;
+        }
+    }
+}
+
+// sum += the products of scalar row a over the blocks lo <= b < hi that store it
+// (masks and first rows in LDS), in block order; rows outside [v0, v1) are left to
+// other passes.  Four blocks' LDS reads at a time.
+__device__ inline void add_stored_rows(const uint32_t *bmask, const int *bq, const double *dot, int lo, int hi, int a,
+                                       int v0, int v1, double &sum) {
+    const uint32_t below = (1u << a) - 1u;
+    for (int b = lo; b < hi; b += 4) {
+        bool ok[4];
+        double d[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int t = min(b + k, hi - 1);
+            const uint32_t m = bmask[t];
+            const int v = bq[t] + __popc(m & below);
+            ok[k] = b + k < hi && ((m >> a) & 1u) && v >= v0 && v < v1;
+            d[k] = dot[ok[k] ? v - v0 : 0];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sum = ok[k] ? sum + d[k] : sum;
+    }
+}
+
 // The same restriction with one lane per stored row of Z (block sizes >= 8,
 // where a block row's lanes would mostly wait: a Z block has a few nonzero
 // rows, a face's worth).  The R coarse rows of a workgroup own the stored rows
@@ -955,11 +1035,19 @@ __global__ __launch_bounds__(kThreads) void k_restrict_cr(const int *__restrict_
     // the rows' block ranges and (when few enough) the blocks' masks and first stored rows, in LDS
     const bool staged = t1 - t0 <= kCrBlk;
     for (int k = threadIdx.x; k <= i1 - i0; k += kThreads) rowb[k] = zrp[i0 + k];
-    if (staged)
+    // (a staged block's column waits in its thread's registers)
+    int Jb[kCrBlk / kThreads] = {};
+    if (staged) {
+#pragma unroll
+        for (int k = 0; k < kCrBlk / kThreads; ++k) {
+            const int t = t0 + static_cast<int>(threadIdx.x) + k * kThreads;
+            if (t < t1) Jb[k] = zcol[t];
+        }
         for (int t = t0 + static_cast<int>(threadIdx.x); t <= t1; t += kThreads) {
             bq[t - t0] = first_row_g(t);
-            if (RB && t < t1) bmask[t - t0] = zr.mask[t];
+            if (t < t1) bmask[t - t0] = RB ? zr.mask[t] : ~0u;
         }
+    }
     const int nout = (i1 - i0) * bs;   // <= 2 kThreads (host)
     // r_C loads while the products run
     double rv[2] = {0.0, 0.0};
@@ -977,33 +1065,36 @@ __global__ __launch_bounds__(kThreads) void k_restrict_cr(const int *__restrict_
     double acc[2] = {0.0, 0.0};
     for (int qc = q0; qc < q1; qc += kCrCap) {
         const int qe = min(q1, qc + kCrCap);
-        for (int t = t0 + static_cast<int>(threadIdx.x); t < t1; t += kThreads) {
+        auto columns = [&](int t, int J) {
             const int lo = max(first_row(t), qc), hi = min(first_row(t + 1), qe);
-            if (lo < hi) {
-                const int J = zcol[t];
-                for (int q = lo; q < hi; ++q) qcol[q - qc] = J;
+            for (int q = lo; q < hi; ++q) qcol[q - qc] = J;
+        };
+        if (staged) {
+#pragma unroll
+            for (int k = 0; k < kCrBlk / kThreads; ++k) {
+                const int t = t0 + static_cast<int>(threadIdx.x) + k * kThreads;
+                if (t < t1) columns(t, Jb[k]);
             }
+        } else {
+            for (int t = t0 + static_cast<int>(threadIdx.x); t < t1; t += kThreads) columns(t, zcol[t]);
         }
         __syncthreads();
-        for (int q = qc + static_cast<int>(threadIdx.x); q < qe; q += kThreads)
-            dot[q - qc] = block_row_dot<BS>(vals + static_cast<int64_t>(q) * bs, r + static_cast<int64_t>(qcol[q - qc]) * bs,
-                                            bs);
+        stored_row_dots<BS, false, true>(vals, r, qcol, dot, qc, qe, bs, [](int q) { return static_cast<int64_t>(q); });
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int k = static_cast<int>(threadIdx.x) + j * kThreads;
             if (k < nout) {
                 const int il = k / bs, a = k - (k / bs) * bs;
-                const int hi = rowb[il + 1];
-                for (int t = rowb[il]; t < hi; ++t) {
-                    int q;
-                    if constexpr (RB) {
-                        const uint32_t m = staged ? bmask[t - t0] : zr.mask[t];
-                        if (!((m >> a) & 1u)) continue;
-                        q = first_row(t) + __popc(m & ((1u << a) - 1u));
-                    } else {
-                        q = t * bs + a;
-                    }
+                const int lo = rowb[il], hi = rowb[il + 1];
+                if (staged) {
+                    add_stored_rows(bmask, bq, dot, lo - t0, hi - t0, a, qc, qe, acc[j]);
+                    continue;
+                }
+                for (int t = lo; t < hi; ++t) {
+                    const uint32_t m = RB ? zr.mask[t] : ~0u;
+                    if (!((m >> a) & 1u)) continue;
+                    const int q = first_row_g(t) + __popc(m & ((1u << a) - 1u));
                     if (q >= qc && q < qe) acc[j] += dot[q - qc];
                 }
             }
@@ -1166,45 +1257,56 @@ __device__ inline void split_products(SplitLds &lds, const SplitView<MT> &S, int
         lds.rowb[0][k] = FIRST ? S.rowptr[f0 + k] - tc0 : 0;
         lds.rowb[1][k] = nbc + S.rowptr[S.nF + f0 + k] - tf0;
     }
-    if (staged)
+    int Jb[kCrBlk / kThreads] = {};   // (a staged block's column waits in its thread's registers)
+    if (staged) {
+#pragma unroll
+        for (int k = 0; k < kCrBlk / kThreads; ++k) {
+            const int b = static_cast<int>(threadIdx.x) + k * kThreads;
+            if (b < nbt) Jb[k] = cols[block(b)];
+        }
         for (int b = threadIdx.x; b <= nbt; b += kThreads) {
             lds.bq[b] = first_g(b);
             if (b < nbt) lds.bmask[b] = RB.mask[block(b)];
         }
+    }
     __syncthreads();
     auto first = [&](int b) { return staged ? lds.bq[b] : first_g(b); };
     const int nq = first(nbt);
     const int nout = (f1 - f0) * bs;
     for (int v0 = 0; v0 < nq; v0 += kCrCap) {
         const int v1 = min(nq, v0 + kCrCap);
-        for (int b = threadIdx.x; b < nbt; b += kThreads) {
+        auto columns = [&](int b, int J) {
             const int lo = max(first(b), v0), hi = min(first(b + 1), v1);
-            if (lo < hi) {
-                const int J = cols[block(b)];
-                for (int v = lo; v < hi; ++v) lds.qcol[v - v0] = J;
+            for (int v = lo; v < hi; ++v) lds.qcol[v - v0] = J;
+        };
+        if (staged) {
+#pragma unroll
+            for (int k = 0; k < kCrBlk / kThreads; ++k) {
+                const int b = static_cast<int>(threadIdx.x) + k * kThreads;
+                if (b < nbt) columns(b, Jb[k]);
             }
+        } else {
+            for (int b = threadIdx.x; b < nbt; b += kThreads) columns(b, cols[block(b)]);
         }
         __syncthreads();
-        for (int v = v0 + static_cast<int>(threadIdx.x); v < v1; v += kThreads) {
-            const int J = lds.qcol[v - v0];
-            const int64_t q = v < nqc ? qc0 + v : qf0 + v;
-            // (the first sweep's coarse columns: negative where P has no row)
-            lds.dot[v - v0] = !FIRST || J >= 0
-                                  ? block_row_dot<BS>(RB.vals + q * bs, x + static_cast<int64_t>(J) * bs, bs)
-                                  : 0.0;
-        }
+        // (the first sweep's coarse columns: negative where P has no row)
+        stored_row_dots<BS, FIRST, FIRST>(RB.vals, x, lds.qcol, lds.dot, v0, v1, bs,
+                            [&](int v) { return static_cast<int64_t>(v < nqc ? qc0 + v : qf0 + v); });
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int k = static_cast<int>(threadIdx.x) + j * kThreads;
             if (k < nout) {
                 const int il = k / bs, a = k - il * bs;
-                const uint32_t below = (1u << a) - 1u;
                 auto add = [&](int lo, int hi, double &sum) {
+                    if (staged) {
+                        add_stored_rows(lds.bmask, lds.bq, lds.dot, lo, hi, a, v0, v1, sum);
+                        return;
+                    }
                     for (int b = lo; b < hi; ++b) {
-                        const uint32_t m = staged ? lds.bmask[b] : RB.mask[block(b)];
+                        const uint32_t m = RB.mask[block(b)];
                         if (!((m >> a) & 1u)) continue;
-                        const int v = first(b) + __popc(m & below);
+                        const int v = first_g(b) + __popc(m & ((1u << a) - 1u));
                         if (v >= v0 && v < v1) sum += lds.dot[v - v0];
                     }
                 };
