@@ -568,15 +568,20 @@ void make_fp32_copies(Hier &h, hipStream_t s) {
             L.e1_32.alloc(n);
             L.tmp32.alloc(n);
         }
-        // every level's operator (the F-cycle's coarse solve takes a residual
-        // on the coarsest level too); Z only where the level coarsens
-        if (!L.vals32.get()) {
+        // Every level's operator whose blocks a cycle reads whole: not those of a V-cycle's
+        // split levels, whose sweeps read the split copy alone (8 ms of a 94 ms setup at 64
+        // Q2 transport operators went into such copies); with FC relaxation the C sweep
+        // reads A, in an F-cycle the coarse solve's residual does, on the coarsest level
+        // too.  Z only where the level coarsens and keeps no row copy, which the
+        // restriction reads instead.
+        const bool whole = !L.split.on || h.prm.relax == 1 || h.prm.cycle == 1;
+        if (whole && !L.vals32.get()) {
             L.vals32.alloc(static_cast<size_t>(L.A.nnzb * bb));
             launch_to_float(L.A.vals.get(), L.vals32.get(), L.A.nnzb * bb, s);
-            if (!L.coarsest && !L.zrows.on) {   // (with a row-compressed Z the restriction reads only that)
-                L.z32.alloc(static_cast<size_t>(L.Z.nnzb * bb));
-                launch_to_float(L.Z.vals.get(), L.z32.get(), L.Z.nnzb * bb, s);
-            }
+        }
+        if (!L.coarsest && !L.zrows.on && !L.z32.get()) {
+            L.z32.alloc(static_cast<size_t>(L.Z.nnzb * bb));
+            launch_to_float(L.Z.vals.get(), L.z32.get(), L.Z.nnzb * bb, s);
         }
         if (L.have_T && L.AT.rowptr.get() && !L.at32.get()) {
             L.at32.alloc(static_cast<size_t>(L.AT.nnzb * bb));
