@@ -5,6 +5,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <cstring>
 #include <initializer_list>
 #include <string>
 #include <vector>
@@ -206,19 +207,35 @@ struct FillInts {
     int v;
 };
 void launch_fill_ints(std::initializer_list<FillInts> jobs, hipStream_t s);
-// margin[2] += F rows whose chosen C block has a rival within 1e-12 relative
-void launch_one_point(const int *rowptr, const int *colidx, const double *bnorm, const int8_t *cf,
-                      const int *cidx, int nb, int *pmap, int *margin, hipStream_t s);
-// T = -(Dinv_I A_IJ) over phi-strong F-F blocks (fine row numbering, C rows empty)
-void launch_count_T(const int *rowptr, const int *colidx, const uint8_t *mask, const int8_t *cf, int nb,
-                    int *cnt, hipStream_t s);
-void launch_fill_T(const int *rowptr, const int *colidx, const uint8_t *mask, const int8_t *cf, int nb,
-                   const int *trowptr, int *tcol, int *trow, int *tsrc, hipStream_t s);
-// W0 = A_cf (coarse rows)
-void launch_count_Acf(const int *rowptr, const int *colidx, const int8_t *cf, const int *cpts, int nc,
-                      int *cnt, hipStream_t s);
-void launch_fill_Acf(const int *rowptr, const int *colidx, const int8_t *cf, const int *cpts, int nc,
-                     const int *wrowptr, int *wcol, int *wsrc, hipStream_t s);
+// Words that travel in a launch's arguments, to several device arrays: the host's
+// copies may go as soon as the call returns.  add() is false when they do not fit.
+struct PutJobs {
+    static constexpr int kMax = 8, kWords = 128;
+    uint32_t *dst[kMax];
+    int words[kMax];
+    uint32_t data[kWords];
+    int k = 0, used = 0;
+    bool add(void *to, const void *from, size_t bytes) {
+        const int n = static_cast<int>(bytes / 4);
+        if (k == kMax || bytes % 4 != 0 || bytes > 4 * kWords || used + n > kWords) return false;
+        std::memcpy(data + used, from, bytes);
+        dst[k] = static_cast<uint32_t *>(to);
+        words[k++] = n;
+        used += n;
+        return true;
+    }
+};
+void launch_put_words(const PutJobs &J, hipStream_t s);
+// After the splitting, one pass over the rows: the one-point map (margin[2] += F rows
+// whose chosen C block has a rival within 1e-12 relative), T's blocks per row
+// (T = -(Dinv_I A_IJ) over phi-strong F-F blocks; fine row numbering, C rows empty) and
+// those of W0 = A_cf (coarse rows); then both patterns.
+void launch_split_rows(const int *rowptr, const int *colidx, const uint8_t *mask, const double *bnorm,
+                       const int8_t *cf, const int *cidx, int nb, int *pmap, int *margin, int *cntT, int *cntW,
+                       hipStream_t s);
+void launch_split_fill_rows(const int *rowptr, const int *colidx, const uint8_t *mask, const int8_t *cf,
+                            const int *cidx, int nb, const int *trowptr, int *tcol, int *trow, int *tsrc,
+                            const int *wrowptr, int *wcol, int *wsrc, hipStream_t s);
 // out[t] = sign * (X[xi[t]] * Y[yi[t]]) for n blocks (fma chain, c ascending);
 // count (device, nullable): only the first *count <= n blocks; rmask
 // (nullable, 9x9 and 16x16 blocks): each product's nonzero rows as a bit mask
@@ -257,7 +274,9 @@ void launch_rows_of(const int *rowptr, int nrows, int *rowid, hipStream_t s);
 // C = X * Y (+ optional implicit identity block of X at column xdiag[i]).
 // Fixed accumulation order: inner index ascending, c ascending, one fma chain.
 // (xmap: X's values are not stored with it; X's block x is block xmap[x] of xvals)
-void spgemm(const DevBSR &X, const int *xdiag, const DevBSR &Y, DevBSR &C, hipStream_t s,
+// zeros: kSpgemmZeros device words, zero on entry, that the call may change
+constexpr int kSpgemmZeros = 4;
+void spgemm(const DevBSR &X, const int *xdiag, const DevBSR &Y, DevBSR &C, int *zeros, hipStream_t s,
             const double *xvals = nullptr, const int *xmap = nullptr);
 // O = S + W (union pattern, S's value first).  O's block count stays on the
 // device (O.nnzb = -1, arrays of S.bound() + W.bound() blocks).
@@ -278,8 +297,9 @@ void bsr_add(const DevBSR &S, const DevBSR &W, DevBSR &O, hipStream_t s, DBuf<in
 // read back with the first synchronisation.
 // kmask receives the row masks of K's kept blocks where the fused kernel forms
 // them (9x9 and 16x16 blocks; left unallocated otherwise).
+// zeros: 2 kSpgemmZeros words as spgemm's
 void galerkin(DevBSR &Z, const int *cpts, const DevBSR &A, const int *pmap, int nc, double drop, DevBSR &K,
-              int *margin, DBuf<double> &knext, DBuf<uint32_t> &kmask, hipStream_t s);
+              int *margin, DBuf<double> &knext, DBuf<uint32_t> &kmask, int *zeros, hipStream_t s);
 
 // ------------------------------------------------------------------ dense
 // For each segment k < nseg (host arrays): the dense operator of A's block rows

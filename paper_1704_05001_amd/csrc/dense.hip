@@ -506,12 +506,20 @@ int dense_inverse_segments(const DevBSR &A, int nseg, const int *blk0_h, const i
     DBuf<int> blk0(nseg), nbk(nseg), sing(nseg), sel(sel_lds.empty() ? 1 : sel_lds.size());
     DBuf<int64_t> off(nseg);
     NAIR_HIP(hipMemsetAsync(M.get(), 0, sizeof(double) * static_cast<size_t>(total), s));
-    NAIR_HIP(hipMemsetAsync(sing.get(), 0, sizeof(int) * nseg, s));
-    NAIR_HIP(hipMemcpyAsync(blk0.get(), blk0_h, sizeof(int) * nseg, hipMemcpyHostToDevice, s));
-    NAIR_HIP(hipMemcpyAsync(nbk.get(), nbk_h, sizeof(int) * nseg, hipMemcpyHostToDevice, s));
-    NAIR_HIP(hipMemcpyAsync(off.get(), off_h, sizeof(int64_t) * nseg, hipMemcpyHostToDevice, s));
-    if (!sel_lds.empty())
-        NAIR_HIP(hipMemcpyAsync(sel.get(), sel_lds.data(), sizeof(int) * sel_lds.size(), hipMemcpyHostToDevice, s));
+    const std::vector<int> none(static_cast<size_t>(nseg), 0);
+    const size_t ib = sizeof(int) * static_cast<size_t>(nseg);
+    PutJobs J;
+    if (J.add(sing.get(), none.data(), ib) && J.add(blk0.get(), blk0_h, ib) && J.add(nbk.get(), nbk_h, ib) &&
+        J.add(off.get(), off_h, 2 * ib) && J.add(sel.get(), sel_lds.data(), sizeof(int) * sel_lds.size())) {
+        launch_put_words(J, s);
+    } else {
+        NAIR_HIP(hipMemsetAsync(sing.get(), 0, ib, s));
+        NAIR_HIP(hipMemcpyAsync(blk0.get(), blk0_h, ib, hipMemcpyHostToDevice, s));
+        NAIR_HIP(hipMemcpyAsync(nbk.get(), nbk_h, ib, hipMemcpyHostToDevice, s));
+        NAIR_HIP(hipMemcpyAsync(off.get(), off_h, 2 * ib, hipMemcpyHostToDevice, s));
+        if (!sel_lds.empty())
+            NAIR_HIP(hipMemcpyAsync(sel.get(), sel_lds.data(), sizeof(int) * sel_lds.size(), hipMemcpyHostToDevice, s));
+    }
     k_bsr_to_dense<<<dim3(static_cast<unsigned>(max_nb), static_cast<unsigned>(nseg)), 256, 0, s>>>(
         A.rowptr.get(), A.colidx.get(), A.vals.get(), bs, blk0.get(), nbk.get(), off.get(), M.get());
     NAIR_HIP(hipGetLastError());
@@ -575,14 +583,14 @@ int dense_inverse_segments(const DevBSR &A, int nseg, const int *blk0_h, const i
             M.get(), seld, nbk.get(), bs, off.get(), poff, prow, upos, sing.get(), inv);
         NAIR_HIP(hipGetLastError());
     }
+    // (the flags come back with the transposes done: the host arrays and temporaries end here)
+    k_transpose_dense<<<dim3(grid_for(max_n * max_n, 256), static_cast<unsigned>(nseg)), 256, 0, s>>>(
+        inv, invT, nbk.get(), bs, off.get());
+    NAIR_HIP(hipGetLastError());
     std::vector<int> hs(nseg);
     read_ints(sing.get(), hs.data(), nseg, s);
     for (int k = 0; k < nseg; ++k)
         if (hs[k] != 0) return k;
-    k_transpose_dense<<<dim3(grid_for(max_n * max_n, 256), static_cast<unsigned>(nseg)), 256, 0, s>>>(
-        inv, invT, nbk.get(), bs, off.get());
-    NAIR_HIP(hipGetLastError());
-    NAIR_HIP(hipStreamSynchronize(s));   // the host arrays and temporaries end here
     return -1;
 }
 

@@ -88,10 +88,17 @@ void make_direct(Level &L, int lvl, hipStream_t s) {
     L.dn_d.alloc(L.ndseg);
     L.dsys_d.alloc(L.ndseg);
     L.doff_d.alloc(L.ndseg);
-    NAIR_HIP(hipMemcpyAsync(L.dsys_d.get(), L.dsys.data(), sizeof(int) * L.ndseg, hipMemcpyHostToDevice, s));
-    NAIR_HIP(hipMemcpyAsync(L.ddof0_d.get(), dof0.data(), sizeof(int) * L.ndseg, hipMemcpyHostToDevice, s));
-    NAIR_HIP(hipMemcpyAsync(L.dn_d.get(), nn.data(), sizeof(int) * L.ndseg, hipMemcpyHostToDevice, s));
-    NAIR_HIP(hipMemcpyAsync(L.doff_d.get(), L.doff.data(), sizeof(int64_t) * L.ndseg, hipMemcpyHostToDevice, s));
+    const size_t ib = sizeof(int) * static_cast<size_t>(L.ndseg), ob = 2 * ib;
+    PutJobs J;
+    if (J.add(L.dsys_d.get(), L.dsys.data(), ib) && J.add(L.ddof0_d.get(), dof0.data(), ib) &&
+        J.add(L.dn_d.get(), nn.data(), ib) && J.add(L.doff_d.get(), L.doff.data(), ob)) {
+        launch_put_words(J, s);
+        return;
+    }
+    NAIR_HIP(hipMemcpyAsync(L.dsys_d.get(), L.dsys.data(), ib, hipMemcpyHostToDevice, s));
+    NAIR_HIP(hipMemcpyAsync(L.ddof0_d.get(), dof0.data(), ib, hipMemcpyHostToDevice, s));
+    NAIR_HIP(hipMemcpyAsync(L.dn_d.get(), nn.data(), ib, hipMemcpyHostToDevice, s));
+    NAIR_HIP(hipMemcpyAsync(L.doff_d.get(), L.doff.data(), ob, hipMemcpyHostToDevice, s));
     NAIR_HIP(hipStreamSynchronize(s));   // dof0 and nn are pageable host memory
 }
 
@@ -281,7 +288,13 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
         L.dround.alloc(n);
         DBuf<int> sing(1);
         L.margin.alloc(4);
-        launch_fill_ints({{sing.get(), 1, kNoSingular}, {L.lambda.get(), n, 0}, {L.margin.get(), 4, 0}}, s);
+        // the level's sparse products' flags: one product per Neumann step, two steps of the Galerkin product
+        DBuf<int> zeros(static_cast<size_t>(kSpgemmZeros) * (p.degree + 2));
+        launch_fill_ints({{sing.get(), 1, kNoSingular},
+                          {L.lambda.get(), n, 0},
+                          {L.margin.get(), 4, 0},
+                          {zeros.get(), kSpgemmZeros * (static_cast<int64_t>(p.degree) + 2), 0}},
+                         s);
         if (!L.bnorm_ready) {
             if (l == 0 && copy_from) {   // the caller's values: copied here; the face copy's masks come along
                 if (p.faces == 1) L.facemeta.alloc(static_cast<size_t>(nz));
@@ -387,8 +400,6 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
             L.flist.alloc(L.nF);
             launch_cf_index(L.cf.get(), cscan.get(), fscan.get(), n, L.cidx.get(), L.cpts.get(), L.flist.get(), s);
         }
-        launch_one_point(L.A.rowptr.get(), L.A.colidx.get(), L.bnorm.get(), L.cf.get(), L.cidx.get(), n,
-                         L.pmap.get(), L.margin.get(), s);
         // Neumann operands: T (phi-strong F-F, scaled by -D_ff^{-1}) and W_0 = A_cf
         DevBSR T, W0;
         T.nb = n;
@@ -402,8 +413,8 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
         int tot[2] = {0, 0};   // blocks of T and of W_0, side by side for one copy
         {
             DBuf<int> cntT(n), cntW(nc), dtot(2);
-            launch_count_T(L.A.rowptr.get(), L.A.colidx.get(), L.mask.get(), L.cf.get(), n, cntT.get(), s);
-            launch_count_Acf(L.A.rowptr.get(), L.A.colidx.get(), L.cf.get(), L.cpts.get(), nc, cntW.get(), s);
+            launch_split_rows(L.A.rowptr.get(), L.A.colidx.get(), L.mask.get(), L.bnorm.get(), L.cf.get(),
+                              L.cidx.get(), n, L.pmap.get(), L.margin.get(), cntT.get(), cntW.get(), s);
             scan_exclusive2(cntT.get(), T.rowptr.get(), n, dtot.get(), cntW.get(), W0.rowptr.get(), nc, dtot.get() + 1,
                             s);
             read_ints(dtot.get(), tot, 2, s);
@@ -412,21 +423,20 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
         T.nnzb = nT;
         T.colidx.alloc(nT);
         T.vals.alloc(static_cast<size_t>(nT) * bb);
-        {
-            DBuf<int> trow(nT), tsrc(nT);
-            launch_fill_T(L.A.rowptr.get(), L.A.colidx.get(), L.mask.get(), L.cf.get(), n, T.rowptr.get(),
-                          T.colidx.get(), trow.get(), tsrc.get(), s);
-            TimerScope ts(TK_BLOCKPROD, l, s);
-            launch_block_product(nT, bs, L.dinv.get(), trow.get(), L.A.vals.get(), tsrc.get(), -1.0, T.vals.get(),
-                                 s);
-        }
         // (on the matrix cores W_0 keeps no values of its own: its block t is A's block wsrc[t])
         const bool masks = use_matrix_cores(bs);   // the matrix-core products give each block's nonzero rows
         W0.nnzb = nW;
         W0.colidx.alloc(nW);
         DBuf<int> wsrc(nW);
-        launch_fill_Acf(L.A.rowptr.get(), L.A.colidx.get(), L.cf.get(), L.cpts.get(), nc, W0.rowptr.get(),
-                        W0.colidx.get(), wsrc.get(), s);
+        {
+            DBuf<int> trow(nT), tsrc(nT);
+            launch_split_fill_rows(L.A.rowptr.get(), L.A.colidx.get(), L.mask.get(), L.cf.get(), L.cidx.get(), n,
+                                   T.rowptr.get(), T.colidx.get(), trow.get(), tsrc.get(), W0.rowptr.get(),
+                                   W0.colidx.get(), wsrc.get(), s);
+            TimerScope ts(TK_BLOCKPROD, l, s);
+            launch_block_product(nT, bs, L.dinv.get(), trow.get(), L.A.vals.get(), tsrc.get(), -1.0, T.vals.get(),
+                                 s);
+        }
         if (!masks) {
             W0.vals.alloc(static_cast<size_t>(nW) * bb);
             launch_block_gather(nW, bs, L.A.vals.get(), wsrc.get(), W0.vals.get(), s);
@@ -443,9 +453,9 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
         for (int d = 1; d <= p.degree; ++d) {
             DevBSR Wd;
             if (masks && d == 1)
-                spgemm(terms[0], nullptr, T, Wd, s, L.A.vals.get(), wsrc.get());
+                spgemm(terms[0], nullptr, T, Wd, zeros.get(), s, L.A.vals.get(), wsrc.get());
             else
-                spgemm(terms.back(), nullptr, T, Wd, s);
+                spgemm(terms.back(), nullptr, T, Wd, zeros.get() + kSpgemmZeros * (d - 1), s);
             DevBSR Snew;
             if (fused_sum) {
                 DBuf<int> mS, mW;
@@ -503,7 +513,8 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
         // Galerkin: K = R A P with R = [Z I], filtered; K's block sizes come along
         auto next = std::make_unique<Level>();
         galerkin(L.Z, L.cpts.get(), L.A, L.pmap.get(), nc, p.drop, next->A, L.margin.get(), next->bnorm,
-                 next->amask, s);
+                 next->amask,
+                 zeros.get() + kSpgemmZeros * static_cast<size_t>(p.degree), s);
         next->bnorm_ready = true;
         next->seg.assign(cseg.begin(), cseg.begin() + nsys + 1);
         next->mode.assign(nsys, 0);

@@ -812,6 +812,14 @@ __global__ __launch_bounds__(256) void k_gather_words(GatherJobs J, uint32_t *__
     if (threadIdx.x == 0) __hip_atomic_store(word, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+__global__ __launch_bounds__(64) void k_put_words(PutJobs J) {
+    int at = 0;
+    for (int k = 0; k < J.k; ++k) {
+        for (int i = threadIdx.x; i < J.words[k]; i += blockDim.x) J.dst[k][i] = J.data[at + i];
+        at += J.words[k];
+    }
+}
+
 struct FillJobs {
     int *p[4];
     int64_t n[4];
@@ -835,29 +843,56 @@ __global__ __launch_bounds__(256) void k_gather_int(const int *__restrict__ v, c
 
 // ------------------------------------------------------ one-point interpolation
 
-// F block: coarse index of its largest (nonzero) stored C block, lowest column on ties.
-__global__ __launch_bounds__(256) void k_one_point(const int *__restrict__ rowptr, const int *__restrict__ colidx,
-                                                  const double *__restrict__ bnorm, const int8_t *__restrict__ cf,
-                                                  const int *__restrict__ cidx, int nb, int *__restrict__ pmap,
-                                                  int *__restrict__ margin) {
+// One pass over each row after the splitting.  F block: the one-point map (coarse
+// index of its largest nonzero stored C block, lowest column on ties) and its blocks
+// of T (phi-strong, F columns); C block: its own index and its blocks of W_0 = A_cf.
+// A row's entries are read four at a time (columns, masks, sizes, then states): a
+// thread's chain of loads bounds it.
+__global__ __launch_bounds__(256) void k_split_rows(const int *__restrict__ rowptr, const int *__restrict__ colidx,
+                                                   const uint8_t *__restrict__ mask,
+                                                   const double *__restrict__ bnorm, const int8_t *__restrict__ cf,
+                                                   const int *__restrict__ cidx, int nb, int *__restrict__ pmap,
+                                                   int *__restrict__ margin, int *__restrict__ cntT,
+                                                   int *__restrict__ cntW) {
     const int I = blockIdx.x * blockDim.x + threadIdx.x;
     if (I >= nb) return;
-    if (cf[I] == kC) {
-        pmap[I] = cidx[I];
-        return;
-    }
-    int best = -1;
+    const int8_t s = cf[I];
+    const int ci = cidx[I], lo = rowptr[I], hi = rowptr[I + 1];
+    int best = -1, nT = 0, nW = 0;
     double bestn = 0.0;
-    for (int t = rowptr[I]; t < rowptr[I + 1]; ++t) {
-        const int J = colidx[t];
-        if (J != I && cf[J] == kC && bnorm[t] > bestn) {
-            bestn = bnorm[t];
-            best = J;
+    for (int t = lo; t < hi; t += 4) {
+        int J[4], m[4];
+        int8_t f[4];
+        double b[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int u = min(t + k, hi - 1);
+            J[k] = colidx[u];
+            m[k] = mask[u];
+            b[k] = bnorm[u];
         }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] = cf[J[k]];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (t + k >= hi) continue;
+            nW += f[k] == kF ? 1 : 0;
+            nT += J[k] != I && f[k] == kF && (m[k] & 2) ? 1 : 0;
+            if (J[k] != I && f[k] == kC && b[k] > bestn) {
+                bestn = b[k];
+                best = J[k];
+            }
+        }
+    }
+    cntT[I] = s == kF ? nT : 0;
+    if (s == kC) {
+        pmap[I] = ci;
+        cntW[ci] = nW;
+        return;
     }
     pmap[I] = (best >= 0) ? cidx[best] : -1;
     if (best >= 0)   // audit: another candidate within 1e-12 of the chosen one's size
-        for (int t = rowptr[I]; t < rowptr[I + 1]; ++t) {
+        for (int t = lo; t < hi; ++t) {
             const int J = colidx[t];
             if (J != I && J != best && cf[J] == kC && bnorm[t] > 0.0 && near_tie(bnorm[t], bestn)) {
                 atomicAdd(margin + 2, 1);
@@ -868,63 +903,44 @@ __global__ __launch_bounds__(256) void k_one_point(const int *__restrict__ rowpt
 
 // ----------------------------------------------- Neumann operands (patterns)
 
-__global__ __launch_bounds__(256) void k_count_T(const int *__restrict__ rowptr, const int *__restrict__ colidx,
-                                                const uint8_t *__restrict__ mask, const int8_t *__restrict__ cf,
-                                                int nb, int *__restrict__ cnt) {
+// T's and W_0's blocks, as k_split_rows counted them (row pointers from the counts).
+__global__ __launch_bounds__(256) void k_split_fill_rows(const int *__restrict__ rowptr, const int *__restrict__ colidx,
+                                                        const uint8_t *__restrict__ mask,
+                                                        const int8_t *__restrict__ cf, const int *__restrict__ cidx,
+                                                        int nb, const int *__restrict__ trowptr,
+                                                        int *__restrict__ tcol, int *__restrict__ trow,
+                                                        int *__restrict__ tsrc, const int *__restrict__ wrowptr,
+                                                        int *__restrict__ wcol, int *__restrict__ wsrc) {
     const int I = blockIdx.x * blockDim.x + threadIdx.x;
     if (I >= nb) return;
-    int c = 0;
-    if (cf[I] == kF)
-        for (int t = rowptr[I]; t < rowptr[I + 1]; ++t) {
-            const int J = colidx[t];
-            c += (J != I && cf[J] == kF && (mask[t] & 2)) ? 1 : 0;
+    const int8_t s = cf[I];
+    if (s != kF && s != kC) return;
+    const int lo = rowptr[I], hi = rowptr[I + 1];
+    int o = s == kF ? trowptr[I] : wrowptr[cidx[I]];
+    for (int t = lo; t < hi; t += 4) {
+        int J[4], m[4];
+        int8_t f[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int u = min(t + k, hi - 1);
+            J[k] = colidx[u];
+            m[k] = mask[u];
         }
-    cnt[I] = c;
-}
-
-__global__ __launch_bounds__(256) void k_fill_T(const int *__restrict__ rowptr, const int *__restrict__ colidx,
-                                               const uint8_t *__restrict__ mask, const int8_t *__restrict__ cf, int nb,
-                                               const int *__restrict__ trowptr, int *__restrict__ tcol,
-                                               int *__restrict__ trow, int *__restrict__ tsrc) {
-    const int I = blockIdx.x * blockDim.x + threadIdx.x;
-    if (I >= nb || cf[I] != kF) return;
-    int o = trowptr[I];
-    for (int t = rowptr[I]; t < rowptr[I + 1]; ++t) {
-        const int J = colidx[t];
-        if (J != I && cf[J] == kF && (mask[t] & 2)) {
-            tcol[o] = J;
-            trow[o] = I;
-            tsrc[o] = t;
-            ++o;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] = cf[J[k]];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (t + k >= hi || f[k] != kF) continue;
+            if (s == kC) {
+                wcol[o] = J[k];
+                wsrc[o++] = t + k;
+            } else if (J[k] != I && (m[k] & 2)) {
+                tcol[o] = J[k];
+                trow[o] = I;
+                tsrc[o++] = t + k;
+            }
         }
     }
-}
-
-__global__ __launch_bounds__(256) void k_count_Acf(const int *__restrict__ rowptr, const int *__restrict__ colidx,
-                                                  const int8_t *__restrict__ cf, const int *__restrict__ cpts, int nc,
-                                                  int *__restrict__ cnt) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nc) return;
-    const int I = cpts[i];
-    int c = 0;
-    for (int t = rowptr[I]; t < rowptr[I + 1]; ++t) c += (cf[colidx[t]] == kF) ? 1 : 0;
-    cnt[i] = c;
-}
-
-__global__ __launch_bounds__(256) void k_fill_Acf(const int *__restrict__ rowptr, const int *__restrict__ colidx,
-                                                 const int8_t *__restrict__ cf, const int *__restrict__ cpts, int nc,
-                                                 const int *__restrict__ wrowptr, int *__restrict__ wcol,
-                                                 int *__restrict__ wsrc) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nc) return;
-    const int I = cpts[i];
-    int o = wrowptr[i];
-    for (int t = rowptr[I]; t < rowptr[I + 1]; ++t)
-        if (cf[colidx[t]] == kF) {
-            wcol[o] = colidx[t];
-            wsrc[o] = t;
-            ++o;
-        }
 }
 
 // out[t] = sign * (X[xi[t]] Y[yi[t]]): entry (a,b) = fma chain over c ascending
@@ -1354,35 +1370,24 @@ void launch_gather_int(const int *v, const int *idx, int n, int *out, hipStream_
     NAIR_HIP(hipGetLastError());
 }
 
-void launch_one_point(const int *rowptr, const int *colidx, const double *bnorm, const int8_t *cf, const int *cidx,
-                      int nb, int *pmap, int *margin, hipStream_t s) {
-    k_one_point<<<grid_for(nb, 256), 256, 0, s>>>(rowptr, colidx, bnorm, cf, cidx, nb, pmap, margin);
+void launch_split_rows(const int *rowptr, const int *colidx, const uint8_t *mask, const double *bnorm,
+                       const int8_t *cf, const int *cidx, int nb, int *pmap, int *margin, int *cntT, int *cntW,
+                       hipStream_t s) {
+    k_split_rows<<<grid_for(nb, 256), 256, 0, s>>>(rowptr, colidx, mask, bnorm, cf, cidx, nb, pmap, margin, cntT, cntW);
     NAIR_HIP(hipGetLastError());
 }
 
-void launch_count_T(const int *rowptr, const int *colidx, const uint8_t *mask, const int8_t *cf, int nb, int *cnt,
-                    hipStream_t s) {
-    k_count_T<<<grid_for(nb, 256), 256, 0, s>>>(rowptr, colidx, mask, cf, nb, cnt);
+void launch_split_fill_rows(const int *rowptr, const int *colidx, const uint8_t *mask, const int8_t *cf,
+                            const int *cidx, int nb, const int *trowptr, int *tcol, int *trow, int *tsrc,
+                            const int *wrowptr, int *wcol, int *wsrc, hipStream_t s) {
+    k_split_fill_rows<<<grid_for(nb, 256), 256, 0, s>>>(rowptr, colidx, mask, cf, cidx, nb, trowptr, tcol, trow, tsrc,
+                                                        wrowptr, wcol, wsrc);
     NAIR_HIP(hipGetLastError());
 }
 
-void launch_fill_T(const int *rowptr, const int *colidx, const uint8_t *mask, const int8_t *cf, int nb,
-                   const int *trowptr, int *tcol, int *trow, int *tsrc, hipStream_t s) {
-    k_fill_T<<<grid_for(nb, 256), 256, 0, s>>>(rowptr, colidx, mask, cf, nb, trowptr, tcol, trow, tsrc);
-    NAIR_HIP(hipGetLastError());
-}
-
-void launch_count_Acf(const int *rowptr, const int *colidx, const int8_t *cf, const int *cpts, int nc, int *cnt,
-                      hipStream_t s) {
-    if (nc <= 0) return;
-    k_count_Acf<<<grid_for(nc, 256), 256, 0, s>>>(rowptr, colidx, cf, cpts, nc, cnt);
-    NAIR_HIP(hipGetLastError());
-}
-
-void launch_fill_Acf(const int *rowptr, const int *colidx, const int8_t *cf, const int *cpts, int nc,
-                     const int *wrowptr, int *wcol, int *wsrc, hipStream_t s) {
-    if (nc <= 0) return;
-    k_fill_Acf<<<grid_for(nc, 256), 256, 0, s>>>(rowptr, colidx, cf, cpts, nc, wrowptr, wcol, wsrc);
+void launch_put_words(const PutJobs &J, hipStream_t s) {
+    if (J.k == 0) return;
+    k_put_words<<<1, 64, 0, s>>>(J);
     NAIR_HIP(hipGetLastError());
 }
 

@@ -329,10 +329,14 @@ __global__ __launch_bounds__(256) void k_merge_rows(MergeArgs M, int *__restrict
     }
 }
 
+// The kept blocks' columns, places, sizes and (rmask) row masks.
 __global__ __launch_bounds__(256) void k_compact_fill(const int *__restrict__ krp, const int *__restrict__ kcol,
-                                                     const uint8_t *__restrict__ keep, int m,
+                                                     const uint8_t *__restrict__ keep,
+                                                     const double *__restrict__ knorm,
+                                                     const uint32_t *__restrict__ kbits, int m,
                                                      const int *__restrict__ orp, int *__restrict__ ocol,
-                                                     int *__restrict__ osrc) {
+                                                     int *__restrict__ osrc, double *__restrict__ onorm,
+                                                     uint32_t *__restrict__ obits) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= m) return;
     int o = orp[i];
@@ -340,6 +344,8 @@ __global__ __launch_bounds__(256) void k_compact_fill(const int *__restrict__ kr
         if (keep[t]) {
             ocol[o] = kcol[t];
             osrc[o] = t;
+            onorm[o] = knorm[t];
+            if (obits) obits[o] = kbits[t];
             ++o;
         }
 }
@@ -847,14 +853,6 @@ void launch_pair_sums(int bs, int64_t nnz, const int *pairptr, const int2 *pairs
     NAIR_HIP(hipGetLastError());
 }
 
-// out[t] = in[src[t]] for t < *count
-__global__ __launch_bounds__(256) void k_gather_mask(int64_t n, const uint32_t *__restrict__ in,
-                                                    const int *__restrict__ src, const int *__restrict__ count,
-                                                    uint32_t *__restrict__ out) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t < n && t < *count) out[t] = in[src[t]];
-}
-
 // --------------------------------------------------- Galerkin merged values
 
 __global__ __launch_bounds__(256) void k_rap_values(int64_t nnz, int bb, const int *__restrict__ kptr,
@@ -1038,7 +1036,8 @@ struct Pairs {
 
 // C's pattern (rowptr, colidx, nnzb) and the pair lists of its blocks; C.vals
 // is left unallocated.
-void spgemm_structure(const DevBSR &X, const int *xdiag, const DevBSR &Y, DevBSR &C, Pairs &P, hipStream_t s) {
+void spgemm_structure(const DevBSR &X, const int *xdiag, const DevBSR &Y, DevBSR &C, Pairs &P, int *flags,
+                      hipStream_t s) {
     const int m = X.nb;
     const int bs = X.bs;
     C.nb = m;
@@ -1052,12 +1051,11 @@ void spgemm_structure(const DevBSR &X, const int *xdiag, const DevBSR &Y, DevBSR
         return;
     }
     // flags: big-row count, too-dense row, then the scans' totals (nnz, pairs), read in one copy
-    DBuf<int> ub(m), cnt(m), big_list(m), flags(4), prow(static_cast<size_t>(m) + 1);
-    NAIR_HIP(hipMemsetAsync(flags.get(), 0, sizeof(int) * 2, s));
-    int *big_count = flags.get();
+    DBuf<int> ub(m), cnt(m), big_list(m), prow(static_cast<size_t>(m) + 1);
+    int *big_count = flags;
     k_row_upper_bound<<<grid_for(m, 256), 256, 0, s>>>(X.rowptr.get(), X.colidx.get(), xdiag, Y.rowptr.get(), m,
                                                       ub.get(), big_list.get(), big_count, kLargeProducts,
-                                                      flags.get() + 1);
+                                                      flags + 1);
     SymArgs S{X.rowptr.get(), X.colidx.get(), xdiag, Y.rowptr.get(), Y.colidx.get(), m, ub.get(), cnt.get()};
     const unsigned gs = cap_grid((m + 15) / 16);
     const bool narrow = Y.ncols < (1 << (32 - kPairBits));   // (column, product) fit 32 bits, no key all ones
@@ -1070,9 +1068,9 @@ void spgemm_structure(const DevBSR &X, const int *xdiag, const DevBSR &Y, DevBSR
         else k_product_large<0, uint64_t><<<kLargeGrid, 256, lds, s>>>(S, big_list.get(), big_count);
     }
     NAIR_HIP(hipGetLastError());
-    scan_exclusive2(cnt.get(), C.rowptr.get(), m, flags.get() + 2, ub.get(), prow.get(), m, flags.get() + 3, s);
+    scan_exclusive2(cnt.get(), C.rowptr.get(), m, flags + 2, ub.get(), prow.get(), m, flags + 3, s);
     int hflags[4] = {0, 0, 0, 0};
-    read_ints(flags.get(), hflags, 4, s);
+    read_ints(flags, hflags, 4, s);
     const int nnz = hflags[2], npairs = hflags[3];
     if (hflags[1] > 0)
         fail(NAIR_ENOMEM, "sparse product row has " + std::to_string(hflags[1]) + " candidate blocks (limit " +
@@ -1120,10 +1118,10 @@ void spgemm_values(const double *xvals, const DevBSR &Y, const Pairs &P, DevBSR 
 
 }  // namespace
 
-void spgemm(const DevBSR &X, const int *xdiag, const DevBSR &Y, DevBSR &C, hipStream_t s, const double *xvals,
-            const int *xmap) {
+void spgemm(const DevBSR &X, const int *xdiag, const DevBSR &Y, DevBSR &C, int *zeros, hipStream_t s,
+            const double *xvals, const int *xmap) {
     Pairs P;
-    spgemm_structure(X, xdiag, Y, C, P, s);
+    spgemm_structure(X, xdiag, Y, C, P, zeros, s);
     if (xmap && P.n > 0) {   // X's block x is block xmap[x] of xvals
         k_remap_x<<<grid_for(P.n, 256), 256, 0, s>>>(P.n, xmap, P.pairs.get());
         NAIR_HIP(hipGetLastError());
@@ -1179,26 +1177,25 @@ namespace {
 // the blocks with several contributors are summed (into `merged`); ymap[t]
 // names block t's values: A's block, or -(merged index)-1 (a lone block is
 // its A block, up to the sign of a zero entry).
-void merge_columns(const DevBSR &A, const int *pmap, int nc, DevBSR &Z, DevBSR &AP, hipStream_t s,
+void merge_columns(const DevBSR &A, const int *pmap, int nc, DevBSR &Z, DevBSR &AP, int *flags, hipStream_t s,
                    DBuf<int> *ymap = nullptr, DBuf<double> *merged = nullptr) {
     const int m = A.nb, bs = A.bs, bb = bs * bs;
     AP.nb = m;
     AP.ncols = nc;
     AP.bs = bs;
-    DBuf<int> cnt(m), ccnt(m), crow(static_cast<size_t>(m) + 1), flags(3);
+    DBuf<int> cnt(m), ccnt(m), crow(static_cast<size_t>(m) + 1);
     AP.rowptr.alloc(static_cast<size_t>(m) + 1);
-    NAIR_HIP(hipMemsetAsync(flags.get(), 0, sizeof(int), s));
     const unsigned gs = cap_grid((m + 15) / 16);
     MergeArgs M{A.rowptr.get(), A.colidx.get(), pmap, m, cnt.get(), ccnt.get()};
     const bool narrow = nc < (1 << (32 - kMergeBits));   // (column, place) fit 32 bits, no key all ones
-    if (narrow) k_merge_rows<0, uint32_t><<<gs, 256, 0, s>>>(M, flags.get());
-    else k_merge_rows<0, uint64_t><<<gs, 256, 0, s>>>(M, flags.get());
+    if (narrow) k_merge_rows<0, uint32_t><<<gs, 256, 0, s>>>(M, flags);
+    else k_merge_rows<0, uint64_t><<<gs, 256, 0, s>>>(M, flags);
     NAIR_HIP(hipGetLastError());
-    scan_exclusive2(cnt.get(), AP.rowptr.get(), m, flags.get() + 1, ccnt.get(), crow.get(), m, flags.get() + 2, s);
+    scan_exclusive2(cnt.get(), AP.rowptr.get(), m, flags + 1, ccnt.get(), crow.get(), m, flags + 2, s);
     int hflags[3] = {0, 0, 0};
     int zcount = 0;
     const bool zdev = Z.nnzb < 0;
-    read_device({{flags.get(), hflags, sizeof(int) * 3},
+    read_device({{flags, hflags, sizeof(int) * 3},
                  {zdev ? Z.rowptr.get() + Z.nb : nullptr, &zcount, zdev ? sizeof(int) : 0}},
                 s);
     if (zdev) Z.nnzb = zcount;
@@ -1216,8 +1213,8 @@ void merge_columns(const DevBSR &A, const int *pmap, int nc, DevBSR &Z, DevBSR &
     M.crow = crow.get();
     M.kptr = kptr.get();
     M.klist = klist.get();
-    if (narrow) k_merge_rows<1, uint32_t><<<gs, 256, 0, s>>>(M, flags.get());
-    else k_merge_rows<1, uint64_t><<<gs, 256, 0, s>>>(M, flags.get());
+    if (narrow) k_merge_rows<1, uint32_t><<<gs, 256, 0, s>>>(M, flags);
+    else k_merge_rows<1, uint64_t><<<gs, 256, 0, s>>>(M, flags);
     if (ymap) {
         DBuf<int> flag(static_cast<size_t>(nnz)), midx(static_cast<size_t>(nnz) + 1);
         k_ap_flags<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, kptr.get(), flag.get());
@@ -1256,7 +1253,7 @@ void merge_columns(const DevBSR &A, const int *pmap, int nc, DevBSR &Z, DevBSR &
 }  // namespace
 
 void galerkin(DevBSR &Z, const int *cpts, const DevBSR &A, const int *pmap, int nc, double drop, DevBSR &K,
-              int *margin, DBuf<double> &knext, DBuf<uint32_t> &kmask, hipStream_t s) {
+              int *margin, DBuf<double> &knext, DBuf<uint32_t> &kmask, int *zeros, hipStream_t s) {
     // A P first (P is one unit block per row: a merge of A's columns), then
     // K = R (A P) with R = [Z I]: its pattern and pair lists, and each block's
     // sum on the matrix cores (with its size and row mask) or by pairs
@@ -1266,10 +1263,10 @@ void galerkin(DevBSR &Z, const int *cpts, const DevBSR &A, const int *pmap, int 
     DevBSR AP;
     DBuf<int> ymap;
     DBuf<double> merged;
-    merge_columns(A, pmap, nc, Z, AP, s, fused ? &ymap : nullptr, fused ? &merged : nullptr);
+    merge_columns(A, pmap, nc, Z, AP, zeros, s, fused ? &ymap : nullptr, fused ? &merged : nullptr);
     DevBSR RK;
     Pairs P;
-    spgemm_structure(Z, cpts, AP, RK, P, s);
+    spgemm_structure(Z, cpts, AP, RK, P, zeros + kSpgemmZeros, s);
     if (fused && P.n > 0) {   // the pairs name A's block or a merged block
         k_remap_y<<<grid_for(P.n, 256), 256, 0, s>>>(P.n, ymap.get(), P.pairs.get());
         NAIR_HIP(hipGetLastError());
@@ -1314,16 +1311,13 @@ void galerkin(DevBSR &Z, const int *cpts, const DevBSR &A, const int *pmap, int 
     knext.alloc(static_cast<size_t>(nnz));
     const int *nk = K.rowptr.get() + m;
     DBuf<int> src(static_cast<size_t>(nnz));
-    k_compact_fill<<<grid_for(m, 256), 256, 0, s>>>(krp, kcol, keep.get(), m, K.rowptr.get(), K.colidx.get(),
-                                                    src.get());
+    if (fused && nnz > 0) kmask.alloc(static_cast<size_t>(nnz));
+    // (a block's size is its max-abs entry)
+    k_compact_fill<<<grid_for(m, 256), 256, 0, s>>>(krp, kcol, keep.get(), knorm.get(), kbits.get(), m,
+                                                    K.rowptr.get(), K.colidx.get(), src.get(), knext.get(),
+                                                    kmask.get());
     NAIR_HIP(hipGetLastError());
     launch_block_gather(nnz, bs, kval.get(), src.get(), K.vals.get(), s, nk);
-    launch_block_gather(nnz, 1, knorm.get(), src.get(), knext.get(), s, nk);   // a block's size is its max-abs entry
-    if (fused && nnz > 0) {
-        kmask.alloc(static_cast<size_t>(nnz));
-        k_gather_mask<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, kbits.get(), src.get(), nk, kmask.get());
-        NAIR_HIP(hipGetLastError());
-    }
 }
 
 }  // namespace nair
