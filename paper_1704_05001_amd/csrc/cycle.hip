@@ -1660,7 +1660,13 @@ __global__ __launch_bounds__(kThreads) void k_seg_sumsq(const double *__restrict
     const double *p = v + clo[c];
     const int len = clen[c];
     double acc = 0.0;
-    for (int i = threadIdx.x; i < len; i += kThreads) acc += p[i] * p[i];
+    for (int i = threadIdx.x; i < len; i += 8 * kThreads) {   // (eight loads before their sums)
+        double x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = p[min(i + k * kThreads, len - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc += i + k * kThreads < len ? x[k] * x[k] : 0.0;
+    }
     const double t = block_reduce_sum(acc, lds);
     if (threadIdx.x == 0) part[c] = t;
 }

@@ -17,7 +17,10 @@ constexpr int kDotVec = 4;                               // basis vectors per pa
 constexpr int kDotWaves = kDotThreads / 64;
 
 // part[i * nblk + blk] = sum over the chunk blk of V_i * w.  Each thread keeps
-// its 8 elements of w in registers and streams kDotVec basis vectors per pass.
+// its 8 elements of w in registers and streams kDotVec basis vectors per pass; the
+// passes are spread over blockIdx.y, since a small problem's chunks alone leave the
+// chip idle (87,025 unknowns are 43 chunks: 15 vectors took 36 us one pass after the
+// other with each load under its bounds check, 6 us this way).
 __global__ __launch_bounds__(kDotThreads) void k_mdot(const double *__restrict__ V, int64_t ld, int nv,
                                                      const double *__restrict__ w, int64_t n,
                                                      double *__restrict__ part, int64_t nblk) {
@@ -27,22 +30,27 @@ __global__ __launch_bounds__(kDotThreads) void k_mdot(const double *__restrict__
 #pragma unroll
     for (int q = 0; q < kDotPer; ++q) {
         const int64_t idx = base + static_cast<int64_t>(q) * kDotThreads;
-        wv[q] = idx < n ? w[idx] : 0.0;
+        const double v = w[idx < n ? idx : n - 1];   // (every load unconditional)
+        wv[q] = idx < n ? v : 0.0;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i0 = 0; i0 < nv; i0 += kDotVec) {
-        double acc[kDotVec];
+    for (int i0 = static_cast<int>(blockIdx.y) * kDotVec; i0 < nv; i0 += static_cast<int>(gridDim.y) * kDotVec) {
+        double acc[kDotVec], x[kDotVec][kDotPer];
+#pragma unroll
+        for (int v = 0; v < kDotVec; ++v) {
+            const double *Vi = V + static_cast<int64_t>(i0 + v < nv ? i0 + v : nv - 1) * ld;
+#pragma unroll
+            for (int q = 0; q < kDotPer; ++q) {
+                const int64_t idx = base + static_cast<int64_t>(q) * kDotThreads;
+                x[v][q] = Vi[idx < n ? idx : n - 1];
+            }
+        }
 #pragma unroll
         for (int v = 0; v < kDotVec; ++v) {
             acc[v] = 0.0;
-            if (i0 + v < nv) {
-                const double *Vi = V + static_cast<int64_t>(i0 + v) * ld;
 #pragma unroll
-                for (int q = 0; q < kDotPer; ++q) {
-                    const int64_t idx = base + static_cast<int64_t>(q) * kDotThreads;
-                    if (idx < n) acc[v] = fma(wv[q], Vi[idx], acc[v]);
-                }
-            }
+            for (int q = 0; q < kDotPer; ++q)
+                if (base + static_cast<int64_t>(q) * kDotThreads < n) acc[v] = fma(wv[q], x[v][q], acc[v]);
         }
 #pragma unroll
         for (int v = 0; v < kDotVec; ++v)
@@ -113,7 +121,10 @@ void launch_mdot(const double *V, int64_t ld, int nv, const double *w, int64_t n
                  hipStream_t s) {
     if (nv <= 0) return;
     const int64_t nblk = mdot_parts(n);
-    k_mdot<<<static_cast<unsigned>(nblk), kDotThreads, 0, s>>>(V, ld, nv, w, n, part, nblk);
+    // (about four workgroups per compute unit: past that the chunks fill the chip by themselves)
+    const int64_t passes = (nv + kDotVec - 1) / kDotVec;
+    const unsigned gy = static_cast<unsigned>(std::min<int64_t>(passes, std::max<int64_t>(1, 1024 / nblk)));
+    k_mdot<<<dim3(static_cast<unsigned>(nblk), gy), kDotThreads, 0, s>>>(V, ld, nv, w, n, part, nblk);
     NAIR_HIP(hipGetLastError());
     k_mdot_finish<<<static_cast<unsigned>(nv), 64, 0, s>>>(part, nblk, out);
     NAIR_HIP(hipGetLastError());
