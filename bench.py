@@ -64,61 +64,68 @@ def measured_traffic(workload: str, grid_threads: int):
     return float(t) if t is not None else None
 
 
-def relax_level_bytes(lv: dict) -> dict:
-    """Algorithmic HBM bytes of one F-relaxation sweep on a level: each operand
-    read once, each output written once (int32 indices, FP64 values).  The
-    sweep e_I = D_I^-1 (r_I - sum_{J != I} A_IJ e_J) reads every off-diagonal
-    block of an F row (from A, where the diagonal block's column index and
-    masks are read too, or from the level's sweep copy, which holds only the
-    off-diagonal blocks); of e, the entries those blocks multiply, each once.
-    With face rectangles an off-diagonal block costs the entries on its
-    nonzero rows and columns plus its 8-byte row/column masks; a sweep copy
-    without them stores each block by its nonzero rows (full width) with a
-    4-byte row mask and a 4-byte offset."""
+def relax_level_bytes(lv: dict, degree: int) -> dict:
+    """Algorithmic HBM bytes of one F sweep on a level, averaged over the
+    degree + 1 sweeps of a cycle visit (each operand read once, each output
+    written once; int32 indices, FP64 values).  On a level of 32,768 lanes or
+    more the first sweep reads every off-diagonal block of the F rows from the
+    split copy, all of D_F^-1, r and e_c, and writes e (s and D^-1 s besides
+    for the rows that still change); a later sweep reads, of those rows alone,
+    the F-F blocks, the columns of D^-1 that they reach, s and D^-1 s.  A block
+    costs 12 bytes and the entries on its nonzero rows and columns (face
+    rectangles) or on its nonzero rows.  A smaller level reads A's whole
+    off-diagonal blocks and D_F^-1 in every sweep."""
     import numpy as np
     rp = lv["rowptr"].cpu().numpy().astype(np.int64)
     cf = lv["cf"].cpu().numpy()
-    bs = lv["bs"]
+    bs, nb = lv["bs"], lv["nb"]
     bb = bs * bs
     rowlen = np.diff(rp)
     F = cf == 0
-    nF = int(F.sum())
+    nF, nC = int(F.sum()), int((cf == 1).sum())
     nnzF = int(rowlen[F].sum())
-    rows = np.repeat(np.arange(lv["nb"]), rowlen)
+    rows = np.repeat(np.arange(nb), rowlen)
     ci = lv["colidx"].cpu().numpy()
-    inF = F[rows]
-    diag = ci == rows
-    off = inF & ~diag
-    copy = lv.get("sweep_nnzb", -1) >= 0
+    off = F[rows] & (ci != rows)
+    split = lv.get("sweep_nnzb", -1) >= 0 and nb * bs >= 32768
+    vec = bs * 8
+    if not split:
+        sweep = nF * (bb * 8 + 16 + 2 * vec) + int(off.sum()) * (bb * 8 + 4) + len(np.unique(ci[off])) * vec
+        return dict(bytes=sweep, nF=nF, nC=nC, nnzF=nnzF, split=False)
     if lv.get("face_meta") is not None:
         meta = lv["face_meta"].cpu().numpy().view(np.uint64)
-        nr = np.bitwise_count(meta & np.uint64(0xFFFFFFFF)).astype(np.int64)
-        nc = np.bitwise_count(meta >> np.uint64(32)).astype(np.int64)
-        bytes_A = (0 if copy else nF * 12) + int((12 + 8 * nr * nc)[off].sum())
-        # e entries needed: per neighbour J, the union of its blocks' nonzero columns
-        cm = np.zeros(lv["nb"], dtype=np.uint64)
-        np.bitwise_or.at(cm, ci[off], meta[off] >> np.uint64(32))
-        bytes_e = int(np.bitwise_count(cm).astype(np.int64).sum()) * 8
-    elif copy:
-        nzr = nonzero_rows(lv["vals"])
-        bytes_A = int((nzr[off] * bs * 8 + 12).sum())
-        bytes_e = len(np.unique(ci[off])) * bs * 8
+        rmask = meta & np.uint64(0xFFFFFFFF)
+        cols = np.bitwise_count(meta >> np.uint64(32)).astype(np.int64)
     else:
-        bytes_A = nF * 4 + int(off.sum()) * (bb * 8 + 4)   # off-diagonal blocks (+ diagonal's index)
-        bytes_e = len(np.unique(ci[off])) * bs * 8
-    bytes_D = nF * bb * 8                  # D_F^{-1}
-    bytes_idx = nF * 4 + nF * 8            # F list, rowptr pairs
-    bytes_vec = bytes_e + nF * bs * 8 * 2  # e gathered (each needed entry once), r_F, e_out_F
-    return dict(bytes=bytes_A + bytes_D + bytes_idx + bytes_vec, nF=nF, nnzF=nnzF,
-                bytes_true_blocks=bytes_A + bytes_D, sweep_copy=copy)
+        nz = (lv["vals"].cpu().numpy() != 0).any(axis=2)
+        rmask = (nz.astype(np.uint64) << np.arange(bs, dtype=np.uint64)).sum(axis=1, dtype=np.uint64)
+        cols = np.full(len(ci), bs, dtype=np.int64)
+    w = 12 + 8 * np.bitwise_count(rmask).astype(np.int64) * cols
+    ff = off & F[ci]
+    moves = np.zeros(nb, dtype=bool)    # rows with an F neighbour: the second sweep changes them
+    moves[rows[ff]] = True
+    moves2 = np.zeros(nb, dtype=bool)   # ... whose F neighbour moves too: so do the sweeps after it
+    moves2[rows[ff & moves[ci]]] = True
+    reach = np.zeros(nb, dtype=np.uint64)
+    np.bitwise_or.at(reach, rows[ff], rmask[ff])
+    reach = np.bitwise_count(reach).astype(np.int64)
+    n1, n2 = int(moves.sum()), int(moves2.sum())
+    total = int(w[off].sum()) + nF * (bb * 8 + 12 + 2 * vec) + nC * 2 * vec + n1 * 2 * vec
+    nu = 1 if n1 == 0 else (min(2, degree + 1) if n2 == 0 else degree + 1)
+    for m in range(2, nu + 1):
+        on = moves if m == 2 else moves2
+        sel = ff & on[rows]
+        total += (int(w[sel].sum()) + int(reach[on].sum()) * vec + int(on.sum()) * (16 + 3 * vec)
+                  + len(np.unique(ci[sel])) * vec)
+    return dict(bytes=total // (degree + 1), nF=nF, nC=nC, nnzF=nnzF, split=True)
 
 
-def sweep_launch_shape(lv: dict, nF: int, tuning, level: int):
-    """The F sweep launch on a level as the library issues it: (kernel, lane
-    groups, grid threads).  A face-compressed copy runs k_sweep with G groups of
-    bs lanes per row; a copy stored by nonzero rows with bs >= 8 on a level of
-    32,768 lanes or more runs k_sweep_cr, R = max(1, 512 / (G bs)) rows per
-    256-thread workgroup."""
+def sweep_launch_shape(lv: dict, rb: dict, tuning, level: int):
+    """The first F sweep launch of a cycle visit as the library issues it:
+    (kernels, lane groups, grid threads).  A large level's split copy runs
+    G groups of bs lanes per row, or, stored by nonzero rows with bs >= 8, one
+    lane per stored row with R = max(1, 512 / (G bs)) F rows per 256-thread
+    workgroup; workgroups for the C rows follow.  A small level runs G groups."""
     G = int(tuning[level][0]) if tuning is not None and len(tuning) > level else 0
     if G <= 0:
         avg_row = lv["nnzb"] / max(1, lv["nb"])
@@ -126,12 +133,13 @@ def sweep_launch_shape(lv: dict, nF: int, tuning, level: int):
     bs = lv["bs"]
     while G > 1 and G * bs > 256:
         G //= 2
-    stored_rows = lv.get("face_meta") is None and lv.get("sweep_nnzb", -1) >= 0
-    if stored_rows and bs >= 8 and nF * bs >= 32768:
-        R = max(1, 512 // (G * bs))
-        return "k_sweep_cr", G, -(-nF // R) * 256
-    rows_per_wg = 256 // (G * bs)
-    return "k_sweep", G, -(-nF // rows_per_wg) * 256
+    c_rows = -(-rb["nC"] * bs // 256)
+    if not rb["split"]:
+        return "k_short_sweep", G, (-(-rb["nF"] // (256 // (G * bs))) + c_rows) * 256
+    stored_rows = lv.get("face_meta") is None and bs >= 8
+    per_wg = max(1, 512 // (G * bs)) if stored_rows else 256 // (G * bs)
+    name = "k_split_first_cr, k_split_next_cr" if stored_rows else "k_split_first, k_split_next"
+    return name, G, (-(-rb["nF"] // per_wg) + c_rows) * 256
 
 
 def H_level0_fields(H):
@@ -173,7 +181,7 @@ def restrict_level_bytes(lv: dict) -> int:
     return bytes_Z + (nc + 1) * 4 + nc * 4 + nc * bs * 16 + nF * bs * 8
 
 
-def level_bandwidth(P, H, b, levels: int) -> list:
+def level_bandwidth(P, H, b, levels: int, degree: int) -> list:
     """Per level: the forward solve's F sweep and restriction, average launch
     time from the library's HIP-event timer over one solve each, and the
     algorithmic GB/s."""
@@ -183,16 +191,19 @@ def level_bandwidth(P, H, b, levels: int) -> list:
         if lv["coarsest"]:
             break
         row = {"level": l, "nb": lv["nb"], "nnzb": lv["nnzb"]}
-        for kind, nbytes in (("relax", relax_level_bytes(H.level(l, fields=("rowptr", "colidx", "cf", "face_meta", "vals")))["bytes"]),
+        for kind, nbytes in (("relax", relax_level_bytes(H.level(l, fields=("rowptr", "colidx", "cf", "face_meta", "vals")), degree)["bytes"]),
                              ("restrict", restrict_level_bytes(lv))):
             P.timer_select(kind, l)
             H.solve(b)
             P.timer_select(None)
             n, ms = P.timer_read()
-            us = ms * 1e3 / max(n, 1)
+            if n == 0:   # below the collapsed coarse solve no sweep or restriction runs
+                row[f"{kind}_us"] = row[f"{kind}_MB"] = row[f"{kind}_GBs"] = None
+                continue
+            us = ms * 1e3 / n
             row[f"{kind}_us"] = round(us, 2)
             row[f"{kind}_MB"] = round(nbytes / 1e6, 2)
-            row[f"{kind}_GBs"] = round(nbytes / (us * 1e-6) / 1e9, 1) if n else None
+            row[f"{kind}_GBs"] = round(nbytes / (us * 1e-6) / 1e9, 1)
         out.append(row)
     return out
 
@@ -559,10 +570,10 @@ def main(argv=None):
 
     def sweep_roof(level, lv, avg_ms, nlaunch):
         """Roofline entry of a level's forward F sweep from its average launch time."""
-        rb = relax_level_bytes(lv)
+        rb = relax_level_bytes(lv, params.degree)
         achieved = rb["bytes"] / (avg_ms * 1e-3) / 1e9
-        name, G, grid_threads = sweep_launch_shape(lv, rb["nF"], tuning, level)
-        return {"bound": "hbm", "kernel": f"{name} (level {level} F sweep)",
+        name, G, grid_threads = sweep_launch_shape(lv, rb, tuning, level)
+        return {"bound": "hbm", "kernel": f"{name} (level {level}, average F sweep of a visit)",
                 "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": measured_traffic(args.workload, grid_threads),
@@ -577,7 +588,7 @@ def main(argv=None):
 
     Hl = P.Hierarchy(rp, ci, va, S.bs, params)
     P.timer_read()
-    levels_bw = level_bandwidth(P, Hl, b, info["levels"])
+    levels_bw = level_bandwidth(P, Hl, b, info["levels"], params.degree)
     Hl_work = Hl
     for r in levels_bw:
         log(f"level {r['level']}: relax {r['relax_us']} us {r['relax_GBs']} GB/s, "

@@ -111,11 +111,13 @@ typedef struct {
                                  zeros are left out: results are bit-identical to faces = 0 for
                                  finite vectors.  Block form only. */
     int32_t sweep_copy;       /* -1 (default): levels whose sweeps occupy at least 32768 lanes (block
-                                 rows x bs) keep a second copy of their F rows, in F-list order and
-                                 without the diagonal blocks, with D_F^{-1} in the same order (and
-                                 the same for A^T once a transposed solve needs it), and the Jacobi
-                                 F sweeps read that contiguously; 0: no copies; 1: every level that
-                                 relaxes.  The sweep computes D_I^{-1}(r_I - sum_{J != I} A_IJ e_J)
+                                 rows x bs) keep a second copy of their F rows without the diagonal
+                                 blocks, the F-F blocks apart from the others and the rows ordered by
+                                 the depth of their F-F couplings, with D_F^{-1} in the same order:
+                                 the Jacobi F sweeps read that contiguously, the later ones of a
+                                 visit only what still changes (and a copy in F-list order of the
+                                 finest A^T once a transposed solve needs it); 0: no copies; 1: every
+                                 level that relaxes.  The sweep computes D_I^{-1}(r_I - sum_{J != I} A_IJ e_J)
                                  either way; with one lane group per row (nair_params.tuning) the
                                  results are bit-identical with and without copies.  Costs about
                                  the F rows' share of each selected operator in memory. */
@@ -171,7 +173,7 @@ typedef struct {
                                       bit-exact with the reference arithmetic either way; the counts
                                       show how close they came to flipping.  A batch counts the rows of
                                       systems solved directly on the level too. */
-    int32_t sweep_nnzb;            /* blocks held by the level's sweep copy of A (nair_params.sweep_copy),
+    int32_t sweep_nnzb;            /* blocks held by the level's sweep or split copy of A (nair_params.sweep_copy),
                                       -1 when its F sweeps read A itself */
 } nair_level_view;
 
@@ -335,8 +337,10 @@ nair_status nair_pool_trim(void);
  * levels) with a pair of HIP events on the launch's stream (the F sweeps of
  * one cycle visit run back to back and are bracketed as one group);
  * kernel = -1 turns the timer off.  Kernels: 0 Jacobi F sweep over
- * the F-row list (both cycles; the FC C sweep and the transposed cycle's first
- * sweep from zero, which reads no matrix, are not timed), 1 outer residual,
+ * the F-row list (both cycles; a forward visit counts k+1 sweeps whether or not
+ * the last ones still change a row; the FC C sweep and the transposed cycle's first
+ * sweep from zero, which reads no matrix, are not timed; levels below a single
+ * system's collapsed coarse cycle run none), 1 outer residual,
  * 2 restriction, 3 interpolation, 4 SpGEMM numeric, 5 SpGEMM symbolic,
  * 6 block inverse,
  * 7 Galerkin blocks (with the R A products where they are fused), 8 dense

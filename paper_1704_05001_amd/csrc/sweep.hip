@@ -1,4 +1,6 @@
-// Sweep copies: the F rows of a level operator (or its transpose) in F-list
+// The sweeps' own copies of F rows.  Split copies (SplitCopy: the forward sweeps
+// of the large levels), short rows (ShortRows: the small levels) and sweep copies:
+// the F rows of a level operator (or its transpose) in F-list
 // order, each without its diagonal block, with D_F^{-1} in the same order
 // (SweepCopy).  A Jacobi F sweep then streams its matrix entries, column
 // indices and inverse blocks contiguously instead of picking F rows out from
