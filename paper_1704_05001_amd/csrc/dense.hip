@@ -179,9 +179,9 @@ constexpr int kPanel = 16;
 // first wave eliminates a panel (two rows per lane, the pivot row broadcast by
 // readlane: no barrier inside a panel), then every wave updates whole 16-column
 // strips, so a strip's pivot rows are read before the wave overwrites them.
-// Bound by the panels' serial chain (about 1 us per column): 166 us at n = 126,
-// where a column at a time over the whole workgroup, with six barriers per
-// column, took 420 us.
+// Bound by the panels' serial chain (below 1 us per column): 112 us at n = 108
+// (140 with the pivot's selects on both rows of a lane), where a column at a time
+// over the whole workgroup, with six barriers per column, took 420 us at n = 126.
 __global__ __launch_bounds__(kInvThreads) void k_invert_lds(const double *__restrict__ Mall,
                                                            double *__restrict__ invall,
                                                            const int *__restrict__ sel, const int *__restrict__ nbk,
@@ -221,11 +221,20 @@ __global__ __launch_bounds__(kInvThreads) void k_invert_lds(const double *__rest
                 ok = ok && best > 0.0;
                 const unsigned long long b0 = __ballot(v0 == best), b1 = __ballot(v1 == best);
                 const int l = __builtin_ctzll(b0 ? b0 : (b1 ? b1 : 1ull));
-                double row[kPanel];
-#pragma unroll
-                for (int j = 0; j < kPanel; ++j) row[j] = b0 ? lane_value(p[0][j], l) : lane_value(p[1][j], l);
+                // (the pivot row's half is the same in every lane: only its rows need the pivot's select)
                 const bool is_piv[2] = {b0 != 0ull && lane == l, b0 == 0ull && lane == l};
-                eliminate<2, kPanel>(p, is_piv, row, c);
+                double row[kPanel];
+                if (b0) {
+#pragma unroll
+                    for (int j = 0; j < kPanel; ++j) row[j] = lane_value(p[0][j], l);
+                    const bool piv[2] = {lane == l, false};
+                    eliminate<2, kPanel>(p, piv, row, c);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < kPanel; ++j) row[j] = lane_value(p[1][j], l);
+                    const bool piv[2] = {false, lane == l};
+                    eliminate<2, kPanel>(p, piv, row, c);
+                }
                 used[0] = used[0] || is_piv[0];
                 used[1] = used[1] || is_piv[1];
                 if (lane == 0 && ok) {

