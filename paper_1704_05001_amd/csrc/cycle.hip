@@ -107,11 +107,20 @@ __device__ inline double face_diag_dot(const FaceView<MT> &F, int I, int a, int 
 // order; NODIAG: the blocks hold no diagonal block, as in a sweep copy)
 constexpr int kFaceUnroll = 8;   // face rectangles up to this many columns take the unrolled row
 
-// NEG: a block in a negative column is left out (its vector block is zero)
+// The F columns' part of a row product that is summed in two parts.
+struct FPart {
+    const int8_t *cf;
+    double sum = 0.0;
+    bool nz = false;   // an F-F block is nonzero in this scalar row
+};
+
+// NEG: a block in a negative column is left out (its vector block is zero).
+// TWO: the blocks in F columns are summed into fp, the others are returned.
 template <int BS, typename MT, typename VT, bool SKIP = false, bool PRE = false, bool NODIAG = false,
-          bool NEG = false>
+          bool NEG = false, bool TWO = false>
 __device__ inline double row_part_face(const int *__restrict__ colidx, const FaceView<MT> &F, int lo, int hi, int g,
-                                       int G, int a, int I, int bs_rt, const VT *__restrict__ x, double pre = 0.0) {
+                                       int G, int a, int I, int bs_rt, const VT *__restrict__ x, double pre = 0.0,
+                                       FPart *fp = nullptr) {
     const int bs = Bs<BS>::get(bs_rt);
     const int64_t bb = static_cast<int64_t>(bs) * bs;
     double acc = 0.0;
@@ -174,7 +183,14 @@ __device__ inline double row_part_face(const int *__restrict__ colidx, const Fac
                         else p0 += static_cast<double>(row[q]) * static_cast<double>(xj[c]);
                     }
                 }
-                acc += p0 + p1;
+                if constexpr (TWO) {
+                    const bool inF = fp->cf[J] == 0;
+                    fp->sum += inF ? p0 + p1 : 0.0;
+                    fp->nz = fp->nz || inF;
+                    acc += inF ? 0.0 : p0 + p1;
+                } else {
+                    acc += p0 + p1;
+                }
             }
         }
         if (tn >= hi) break;
@@ -311,6 +327,25 @@ struct DinvRow {
             for (int c = 0; c < BS; ++c) d[c] = TRANS ? D[c * BS + a] : D[a * BS + c];
         }
     }
+    // as the split sweeps sum it: the columns outside u in one fma chain, then those of u
+    __device__ double apply_split(const double *D, const double *t, int a, int bs, uint32_t u) const {
+        double r = 0.0;
+        if constexpr (BS > 0) {
+            double v[BS];
+#pragma unroll
+            for (int c = 0; c < BS; ++c) v[c] = kPre ? d[kPre ? c : 0] : (TRANS ? D[c * BS + a] : D[a * BS + c]);
+#pragma unroll
+            for (int c = 0; c < BS; ++c) r = (u >> c) & 1u ? r : __builtin_fma(v[c], t[c], r);
+#pragma unroll
+            for (int c = 0; c < BS; ++c) r = (u >> c) & 1u ? __builtin_fma(v[c], t[c], r) : r;
+        } else {
+            for (int c = 0; c < bs; ++c)
+                if (!((u >> c) & 1u)) r = __builtin_fma(TRANS ? D[c * bs + a] : D[a * bs + c], t[c], r);
+            for (int c = 0; c < bs; ++c)
+                if ((u >> c) & 1u) r = __builtin_fma(TRANS ? D[c * bs + a] : D[a * bs + c], t[c], r);
+        }
+        return r;
+    }
     __device__ double apply(const double *D, const double *t, int a, int bs) const {
         if constexpr (kPre) {
             double d0 = 0.0, d1 = 0.0;
@@ -400,47 +435,43 @@ __global__ __launch_bounds__(kThreads) void k_residual(const int *__restrict__ r
     }
 }
 
-// Row I's product with x in two parts: over the columns outside F and over the
-// F columns other than I (sC, sF); nz: whether an F-F block is nonzero in row a.
+// Row I's product with x in two parts: the columns outside F (returned) and the
+// F columns other than I (fp, with whether an F-F block is nonzero in row a).
 template <int BS, bool FACE, typename MT, typename VT>
-__device__ inline void row_product_split(const int *__restrict__ colidx, const MT *__restrict__ vals,
-                                         const FaceView<MT> &F, const int8_t *__restrict__ cf, int lo, int hi, int g,
-                                         int G, int a, int I, int bs_rt, const VT *__restrict__ x, double &sC,
-                                         double &sF, bool &nz) {
+__device__ inline double row_product_split(const int *__restrict__ colidx, const MT *__restrict__ vals,
+                                           const FaceView<MT> &F, int lo, int hi, int g, int G, int a, int I,
+                                           int bs_rt, const VT *__restrict__ x, FPart &fp) {
     const int bs = Bs<BS>::get(bs_rt);
-    for (int t = lo + g; t < hi; t += G) {
-        const int J = colidx[t];
-        if (J == I) continue;
-        const bool inF = cf[J] == 0;
-        double d;
-        bool z = false;
-        if constexpr (FACE) {
-            d = row_part_face<BS, MT, VT, false, false, true>(colidx, F, t, t + 1, 0, 1, a, I, bs, x);
-            z = (static_cast<uint32_t>(F.meta[t]) >> a) & 1u;
-        } else {
+    if constexpr (FACE) {
+        return row_part_face<BS, MT, VT, true, false, false, false, true>(colidx, F, lo, hi, g, G, a, I, bs, x, 0.0,
+                                                                          &fp);
+    } else {
+        double acc = 0.0;
+        for (int t = lo + g; t < hi; t += G) {
+            const int J = colidx[t];
+            if (J == I) continue;
             const MT *blk = vals + (static_cast<int64_t>(t) * bs + a) * bs;
-            d = block_row_dot<BS>(blk, x + static_cast<int64_t>(J) * bs, bs);
-            for (int c = 0; c < bs; ++c) z = z || blk[c] != MT(0);
+            const VT *xj = x + static_cast<int64_t>(J) * bs;
+            const bool inF = fp.cf[J] == 0;
+            double d;
+            bool z = false;
+            if constexpr (BS > 0) {   // (the row's entries stay in registers for the test)
+                MT v[BS];
+#pragma unroll
+                for (int c = 0; c < BS; ++c) v[c] = blk[c];
+                d = block_row_dot<BS>(v, xj, BS);
+#pragma unroll
+                for (int c = 0; c < BS; ++c) z = z || v[c] != MT(0);
+            } else {
+                d = block_row_dot<BS>(blk, xj, bs);
+                for (int c = 0; c < bs; ++c) z = z || blk[c] != MT(0);
+            }
+            fp.sum += inF ? d : 0.0;
+            fp.nz = fp.nz || (inF && z);
+            acc += inF ? 0.0 : d;
         }
-        if (inF) {
-            sF += d;
-            nz = nz || z;
-        } else {
-            sC += d;
-        }
+        return acc;
     }
-}
-
-// D_I^{-1} t for scalar row a as the split sweeps sum it: the columns outside u
-// in one fma chain, then those of u (D row-major).
-template <int BS>
-__device__ inline double apply_dinv_split(const double *__restrict__ D, const double *t, int a, int bs, uint32_t u) {
-    double d = 0.0;
-    for (int c = 0; c < bs; ++c)
-        if (!((u >> c) & 1u)) d = __builtin_fma(D[a * bs + c], t[c], d);
-    for (int c = 0; c < bs; ++c)
-        if ((u >> c) & 1u) d = __builtin_fma(D[a * bs + c], t[c], d);
-    return d;
 }
 
 // One Jacobi sweep over the listed rows (list == nullptr: rows with cf == only_cf;
@@ -601,8 +632,12 @@ __global__ __launch_bounds__(kThreads) void k_relax_T(const int *__restrict__ ro
 }
 
 // The F sweep over a list read from A itself, summed as the split sweeps sum it
-// (levels of at least kFewLanes lanes without copies): every sweep forms s, U,
-// w and t anew.
+// (levels of at least kFewLanes lanes without copies: sweep_copy 0, or copies past
+// int32 offsets): every sweep forms s, U, w and t anew.  Bound by the row's bytes,
+// so they are read once: the entries that are tested for U and the row of D^{-1}
+// stay in registers for both parts of their sums.  A cycle of Q4 160 x 160 cells
+// without copies takes 0.77 ms so; 1.07 ms with the entries read again for the test,
+// a block at a time and D^{-1} entry by entry; 0.79 ms with sums in one part.
 template <int BS, typename MT, typename VT, bool FACE = false>
 __global__ __launch_bounds__(kThreads) void k_relax_split(const int *__restrict__ rowptr,
                                                          const int *__restrict__ colidx, const MT *__restrict__ vals,
@@ -621,23 +656,30 @@ __global__ __launch_bounds__(kThreads) void k_relax_split(const int *__restrict_
     if (L.valid && idx < nlist) I = list[idx];
     if (I >= 0 && !live(gate, I)) I = -1;
     um[threadIdx.x] = 0u;
-    __syncthreads();
-    double sC = 0.0, sF = 0.0;
-    bool nz = false;
-    if (I >= 0) {
-        row_product_split<BS, FACE>(colidx, vals, face, cf, rowptr[I], rowptr[I + 1], L.g, G, L.a, I, bs, ein, sC, sF,
-                                    nz);
-        if (nz) atomicOr(&um[L.lr], 1u << L.a);
-    }
-    sC = reduce_groups(sC, L, G, bs, part);
-    __syncthreads();   // (part is used again)
-    sF = reduce_groups(sF, L, G, bs, part);
+    DinvRow<BS, false> dr;   // (loads ahead of the row product, with r)
+    const double *D = dinv + static_cast<int64_t>(I) * bs * bs;
     const int64_t o = static_cast<int64_t>(I) * bs + L.a;
-    if (I >= 0 && L.g == 0) tb[L.lr * bs + L.a] = (static_cast<double>(r[o]) - sC) - sF;
+    double rv = 0.0;
+    if (I >= 0 && L.g == 0) {
+        rv = static_cast<double>(r[o]);
+        dr.load(D, L.a);
+    }
     __syncthreads();
-    if (I >= 0 && L.g == 0)
-        eout[o] = static_cast<VT>(apply_dinv_split<BS>(dinv + static_cast<int64_t>(I) * bs * bs, tb + L.lr * bs, L.a,
-                                                       bs, um[L.lr]));
+    FPart fp{cf};
+    double sC = 0.0;
+    if (I >= 0) {
+        sC = row_product_split<BS, FACE>(colidx, vals, face, rowptr[I], rowptr[I + 1], L.g, G, L.a, I, bs, ein, fp);
+        if (fp.nz) atomicOr(&um[L.lr], 1u << L.a);
+    }
+    double sF = fp.sum;
+    if (G > 1) {
+        sC = reduce_groups(sC, L, G, bs, part);
+        __syncthreads();   // (part is used again)
+        sF = reduce_groups(sF, L, G, bs, part);
+    }
+    if (I >= 0 && L.g == 0) tb[L.lr * bs + L.a] = (rv - sC) - sF;
+    __syncthreads();
+    if (I >= 0 && L.g == 0) eout[o] = static_cast<VT>(dr.apply_split(D, tb + L.lr * bs, L.a, bs, um[L.lr]));
 }
 
 // Rows of C: efin = e_c (the interpolation's identity rows), by the workgroups of a split first sweep past its F rows'.
