@@ -189,6 +189,16 @@ nair_status nair_default_params(nair_params *p);
  * the filtered Galerkin operator K = R A P; the coarsest level is inverted
  * densely.  A is copied; the caller may free it on return.  *out receives
  * the handle (NULL on error).
+ * Cycles of one system do not visit its small levels one by one: the coarse
+ * solve on the first level below the finest of n <= 2048 unknowns in at most
+ * 1024 block rows (and above the coarsest) is kept as one dense n x n matrix of
+ * doubles (an F-cycle: two, when that is not level 1), and as many transposes
+ * from the first transposed call on: 11 MB each at n = 1192, at most 34.  For a
+ * small problem that is most of the handle (Q1, 32 x 32 cells: 11 of 14 MB).  The
+ * setup's temporaries for it are at most 3 such matrices (F-cycle: 6), given back
+ * before it returns.  Where the pool or the allocator has no room for a matrix the
+ * cycles visit the levels, where it has none for a transpose the transposed cycles
+ * read the matrix by columns: neither fails the call.
  */
 nair_status nair_setup(int32_t nb, int32_t bs, const int32_t *rowptr, const int32_t *colidx,
                        const double *vals, const nair_params *p, void *stream, nair_hier *out);

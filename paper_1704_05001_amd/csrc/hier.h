@@ -203,7 +203,7 @@ struct Hier {
     const int *active = nullptr;    // during a batched solve: per-system "still iterating" flags
     // collapsed coarse cycle (one system): the coarse solve on level `collapse` (0: none) as a
     // dense matrix of the level's unknowns ([0]: of a V-cycle, [1]: of an F-cycle), and the
-    // transposes once a transposed cycle needs them
+    // transposes once a transposed cycle needs them (where there is room for them)
     int collapse = 0;
     DBuf<double> coarse_op[2], coarse_opT[2];
 };

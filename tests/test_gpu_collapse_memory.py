@@ -1,0 +1,121 @@
+"""Memory of the collapsed coarse cycle, seen by a caller's allocator.  Its matrix
+(n x n for the first level below the finest of n <= 2048 unknowns in at most 1024
+block rows) is formed in temporaries of a few such matrices, and it is only a copy of
+what the levels hold: an allocator with no room for it gets a hierarchy whose cycles
+visit the levels, one with no room for its transpose the same transposed solves."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+from nair_inputs import make_config
+from test_gpu_parity import to_dev, np_, _need_gpu, _say, check_solve
+from test_gpu_collapse import check_cycles
+
+pytestmark = pytest.mark.gpu
+
+
+class Memory:
+    """Device memory from torch's allocator: live and peak bytes; blocks of more than `limit` bytes are refused."""
+
+    def __init__(self):
+        self.limit, self.live, self.peak, self.blocks = None, 0, 0, {}
+
+    def callbacks(self, device):
+        from paper_1704_05001_amd import nair as N
+
+        def alloc(nbytes, stream, ctx):
+            if self.limit is not None and nbytes > self.limit:
+                return None
+            p = torch.cuda.caching_allocator_alloc(int(nbytes), 0, int(stream or 0))
+            self.blocks[p] = int(nbytes)
+            self.live += int(nbytes)
+            self.peak = max(self.peak, self.live)
+            return p
+
+        def free(ptr, stream, ctx):
+            self.live -= self.blocks.pop(int(ptr))
+            torch.cuda.caching_allocator_delete(int(ptr))
+
+        a = N._Allocator()
+        keep = (N._ALLOC_FN(alloc), N._FREE_FN(free))
+        a.alloc, a.free, a.ctx = keep[0], keep[1], None
+        return a, keep
+
+
+@pytest.fixture
+def memory(monkeypatch):
+    from paper_1704_05001_amd import nair as N
+    _need_gpu()
+    m = Memory()
+    monkeypatch.setattr(N, "_torch_allocator", m.callbacks)
+    return m
+
+
+def build(S, **kw):
+    import paper_1704_05001_amd as P
+    return P.Hierarchy(*to_dev(S.rowptr, S.colidx, S.vals), S.bs, P.Params(allocator="torch", **kw))
+
+
+def collapsed_order(H):
+    for l in range(1, H.num_levels):
+        lv = H.level(l, fields=())
+        if lv["nb"] * lv["bs"] <= 2048 and lv["nb"] <= 1024:
+            assert not lv["coarsest"]
+            return lv["nb"] * lv["bs"]
+    raise AssertionError("no collapsed level")
+
+
+# temporaries at the collapsed level, in matrices of its order (the level below is no larger): for a V-cycle
+# one array, one coarse array and the matrix below; for an F-cycle three arrays, one coarse array, two matrices below
+@pytest.mark.parametrize("name,N,cycle,most", [("dg_q1_32", 32, "V", 3), ("dg_q1_32", 61, "V", 3),
+                                               ("dg_q2_256_curved", 48, "V", 3), ("dg_q1_32", 32, "F", 6)])
+def test_temporaries_are_a_few_matrices(memory, name, N, cycle, most):
+    _say(f"test: collapsed cycle's temporaries {name} N={N} {cycle}")
+    S, k = make_config(name, N=N)
+    H = build(S, degree=k, cycle=cycle)
+    n = collapsed_order(H)
+    _say(f"  order {n}: {memory.live / 2**20:.1f} MiB live, {(memory.peak - memory.live) / 2**20:.1f} MiB more at the peak")
+    assert memory.peak - memory.live <= most * 8 * n * n
+    H.close()
+    assert memory.live == 0
+
+
+@pytest.mark.parametrize("name,N,kw", [("dg_q1_32", 32, {}), ("dg_q1_32", 32, dict(cycle="F", relax=1)),
+                                       ("dg_q2_256_curved", 24, {}), ("dg_q2_256_curved", 24, dict(cycle="F"))])
+def test_no_room_for_the_matrix(memory, name, N, kw):
+    _say(f"test: no room for the collapsed cycle {name} N={N} {kw}")
+    S, k = make_config(name, N=N)
+    H = build(S, degree=k, **kw)
+    n = collapsed_order(H)
+    H.close()
+    memory.limit = 8 * n * n - 1
+    H = build(S, degree=k, **kw)
+    okw = {a: v for a, v in kw.items() if a != "cycle"}
+    O = oracle.Hierarchy(S.nb, S.bs, S.rowptr, S.colidx, S.vals,
+                         oracle.Params(degree=k, cycle=1 if kw.get("cycle") == "F" else 0, **okw))
+    check_cycles(H, O, S.n, 7)
+    check_solve(H, O, S.rhs)
+    check_solve(H, O, np.random.default_rng(8).uniform(-1, 1, S.n), trans=True)
+    H.close()
+    assert memory.live == 0
+
+
+@pytest.mark.parametrize("kw", [{}, dict(cycle="F"), dict(precision="fp32")])
+def test_no_room_for_the_transpose(memory, kw):
+    """The transposed product then reads the matrix by columns: the same sums."""
+    _say(f"test: no room for the collapsed cycle's transpose {kw}")
+    S, k = make_config("dg_q1_32", N=32)
+    g = torch.from_numpy(np.random.default_rng(9).uniform(-1, 1, S.n)).cuda()
+    out = []
+    for room in (True, False):
+        H = build(S, degree=k, **kw)
+        n = collapsed_order(H)
+        memory.limit = None if room else 8 * n * n - 1
+        y, r = H.solve_T(g)
+        out.append((np_(y).copy(), r.iters, np_(H.vcycle_T(g)).copy()))
+        memory.limit = None
+        H.close()
+    assert out[0][1] == out[1][1]
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][2], out[1][2])
