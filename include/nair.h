@@ -284,7 +284,11 @@ nair_status nair_get_systems(nair_hier h, int32_t lvl, int32_t cap, int32_t *nsy
  */
 nair_status nair_autotune(nair_hier h, int32_t reps, int8_t *table, void *stream);
 
-/* One cycle application e = B r (resp. y = B^T g), zero initial guess. */
+/* One cycle application e = B r (resp. y = B^T g), zero initial guess.  A NaN or
+ * infinity in r makes the entries of e that depend on it non-finite; the others
+ * are what they are without it, except that on the coarsest level of a batch, or of
+ * a system whose coarse cycle is not collapsed (nair_setup), it spreads over all of
+ * the system's unknowns. */
 nair_status nair_vcycle(nair_hier h, const double *r, double *e, void *stream);
 nair_status nair_vcycle_T(nair_hier h, const double *g, double *y, void *stream);
 

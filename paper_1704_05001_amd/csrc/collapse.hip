@@ -274,8 +274,9 @@ __global__ __launch_bounds__(256) void k_collapsed_mv(const double *__restrict__
         mv[i] = j < n ? m[TRANS ? static_cast<int64_t>(j) * n : j] : 0.0;
         xv[i] = j < n ? static_cast<double>(x[j]) : 0.0;
     }
+    // (a zero of M is no dependence: a NaN or infinity of x stays out of the rows that do not depend on it)
 #pragma unroll
-    for (int i = 0; i < kW; ++i) s += mv[i] * xv[i];
+    for (int i = 0; i < kW; ++i) s += mv[i] != 0.0 ? mv[i] * xv[i] : 0.0;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     if (lane == 0) y[row] = static_cast<VT>(s);
