@@ -134,6 +134,11 @@ inline unsigned grid_for(int64_t n, int per_block) {
     return static_cast<unsigned>(g);
 }
 
+// Lets `kernel` take up to `bytes` of dynamic LDS (past 64 KiB a launch needs that) on the
+// current device; asked before each launch, since the limit is the device's.  False
+// when it is refused.
+bool allow_lds(const void *kernel, size_t bytes);
+
 // Synchronous device-to-host reads (small ones staged through pinned memory;
 // several items share one synchronisation).
 struct ReadItem {
@@ -181,7 +186,7 @@ void launch_strong_transpose(const int *rowptr, const int *colidx, const uint8_t
 // splitting states: -1 undecided, 0 F, 1 C, 2 block of a directly solved system
 void launch_pmis_init(const int *lambda, const int8_t *direct, int nb, int8_t *state, int *dround,
                       int *undecided0, hipStream_t s);
-bool split_small_rows(int nb);   // the level's splitting goes out as one launch
+bool split_small_rows(int nb);   // the level's splitting goes out as one launch; asked before each
 void launch_split_small(const int *rowptr, const int *colidx, const uint8_t *mask, const int *lambda, const int *lbase,
                         const int8_t *direct, int nb, int64_t nz, uint64_t seed, int level, int max_rounds, int8_t *cf,
                         int *dround, int *cscan, int *cidx, int *cpts, int *flist, int *out, hipStream_t s);

@@ -496,18 +496,12 @@ int dense_inverse_segments(const DevBSR &A, int nseg, const int *blk0_h, const i
     const int64_t last_n = static_cast<int64_t>(nbk_h[nseg - 1]) * bs;
     const int64_t total = off_h[nseg - 1] + last_n * last_n;
     const int64_t max_n = static_cast<int64_t>(max_nb) * bs;
-    // dynamic LDS beyond 64 KiB needs the attribute; without it every segment takes the panel launches
+    // without the dynamic LDS every segment takes the panel launches
     auto lds_bytes = [](int n) {
         const size_t np = static_cast<size_t>((n + kPanel - 1) / kPanel) * kPanel;
         return sizeof(double) * np * (np + 1);
     };
-    static int lds_ok = -1;
-    if (lds_ok < 0) {
-        lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(k_invert_lds),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     static_cast<int>(lds_bytes(kLdsOrder))) == hipSuccess;
-        if (!lds_ok) (void)hipGetLastError();
-    }
+    const bool lds_ok = allow_lds(reinterpret_cast<const void *>(k_invert_lds), lds_bytes(kLdsOrder));
     std::vector<int> sel_lds, sel_big;
     for (int k = 0; k < nseg; ++k)
         (lds_ok && static_cast<int64_t>(nbk_h[k]) * bs <= kLdsOrder ? sel_lds : sel_big).push_back(k);

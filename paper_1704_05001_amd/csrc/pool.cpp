@@ -22,6 +22,13 @@ void check_hip(hipError_t e, const char *what) {
     }
 }
 
+bool allow_lds(const void *kernel, size_t bytes) {
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes)) == hipSuccess)
+        return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 namespace {
 
 // Size classes: multiples of 256 B up to 64 KiB, then 8 classes per power of two

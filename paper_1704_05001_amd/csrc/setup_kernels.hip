@@ -1304,23 +1304,19 @@ void launch_pmis_round(const int *rowptr, const int *colidx, const uint8_t *mask
     NAIR_HIP(hipGetLastError());
 }
 
-// Whether k_split_small takes a level of nb blocks (and its LDS attribute could be set)
+// Whether k_split_small takes a level of nb blocks (and the device gives it the LDS)
 bool split_small_rows(int nb) {
-    static const bool ok = [] {
-        bool all = true;
-        for (const void *f : {reinterpret_cast<const void *>(k_split_small<1>), reinterpret_cast<const void *>(k_split_small<2>),
-                              reinterpret_cast<const void *>(k_split_small<4>)})
-            all = all && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSplitLds) == hipSuccess;
-        if (!all) (void)hipGetLastError();
-        return all;
-    }();
-    return ok && nb > 0 && nb <= kSplitRows;
+    if (nb <= 0 || nb > kSplitRows) return false;
+    const void *f = nb <= kSplitThreads       ? reinterpret_cast<const void *>(k_split_small<1>)
+                    : nb <= 2 * kSplitThreads ? reinterpret_cast<const void *>(k_split_small<2>)
+                                              : reinterpret_cast<const void *>(k_split_small<4>);
+    return allow_lds(f, kSplitLds);
 }
 
 void launch_split_small(const int *rowptr, const int *colidx, const uint8_t *mask, const int *lambda, const int *lbase,
                         const int8_t *direct, int nb, int64_t nz, uint64_t seed, int level, int max_rounds, int8_t *cf,
                         int *dround, int *cscan, int *cidx, int *cpts, int *flist, int *out, hipStream_t s) {
-    if (!split_small_rows(nb)) fail(NAIR_EDEVICE, "launch_split_small: too many blocks");
+    if (nb <= 0 || nb > kSplitRows) fail(NAIR_EDEVICE, "launch_split_small: too many blocks");
     const int fixed = nb * 14;   // hash, lambda, state, mark
     const int ecap = static_cast<int>(std::min<int64_t>(nz, (kSplitLds - fixed) / 2));
     const size_t lds = static_cast<size_t>(fixed) + 2 * static_cast<size_t>(ecap);

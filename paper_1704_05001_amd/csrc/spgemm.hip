@@ -1091,8 +1091,8 @@ void spgemm_structure(const DevBSR &X, const int *xdiag, const DevBSR &Y, DevBSR
     if (hflags[0] > 0) {
         constexpr size_t lds = (sizeof(uint64_t) + sizeof(int2)) * kLargeProducts;
         auto kern = narrow ? k_product_large<1, uint32_t> : k_product_large<1, uint64_t>;
-        NAIR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+        if (!allow_lds(reinterpret_cast<const void *>(kern), lds))
+            fail(NAIR_EDEVICE, "the device refuses the sparse product's " + std::to_string(lds) + " bytes of LDS");
         kern<<<kLargeGrid, 256, lds, s>>>(S, big_list.get(), big_count);
     }
     NAIR_HIP(hipGetLastError());
