@@ -567,10 +567,11 @@ void build_sweeps(Hier &h, bool trans, hipStream_t s) {
 }
 
 // FP32 copies of what the cycle reads (operators and Z of the non-coarsest
-// levels, and their transposes once built), plus FP32 cycle vectors.
+// levels above the collapsed coarse solve, and their transposes once built), plus
+// FP32 cycle vectors.
 void make_fp32_copies(Hier &h, hipStream_t s) {
-    for (auto &Lp : h.lv) {
-        Level &L = *Lp;
+    for (size_t l = 0; l < h.lv.size(); ++l) {
+        Level &L = *h.lv[l];
         const size_t n = static_cast<size_t>(L.A.nb) * L.A.bs;
         const int64_t bb = static_cast<int64_t>(L.A.bs) * L.A.bs;
         if (!L.r32.get()) {
@@ -579,6 +580,7 @@ void make_fp32_copies(Hier &h, hipStream_t s) {
             L.e1_32.alloc(n);
             L.tmp32.alloc(n);
         }
+        if (h.collapse > 0 && static_cast<int>(l) >= h.collapse) continue;   // (the cycle does not go there)
         // Every level's operator whose blocks a cycle reads whole: not those of a V-cycle's
         // split levels, whose sweeps read the split copy alone (8 ms of a 94 ms setup at 64
         // Q2 transport operators went into such copies); with FC relaxation the C sweep

@@ -119,3 +119,30 @@ def test_no_room_for_the_transpose(memory, kw):
         H.close()
     assert out[0][1] == out[1][1]
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][2], out[1][2])
+
+
+@pytest.mark.parametrize("kw", [{}, dict(sweep_copy="all"), dict(cycle="F", relax=1)])
+def test_no_float_copies_below_the_matrix(memory, kw):
+    """FP32 storage adds float vectors on every level, and float values only above the collapsed level."""
+    _say(f"test: float copies of a collapsed hierarchy {kw}")
+    S, k = make_config("dg_q1_32", N=61)
+    live = {}
+    for prec in ("fp64", "fp32"):
+        H = build(S, degree=k, precision=prec, **kw)
+        n = collapsed_order(H)
+        live[prec] = memory.live
+        lv = [H.level(l, fields=("z_vals", "cf")) for l in range(H.num_levels)]
+        H.close()
+    bb = S.bs * S.bs
+    most = sum(4 * 4 * v["nb"] * S.bs for v in lv)
+    if kw.get("cycle") == "F":   # (the F-cycle keeps its first corrections in float instead of double)
+        most -= sum(4 * v["nb"] * S.bs for v in lv[1:])
+    for v in lv:
+        if v["nb"] * S.bs <= n:
+            break
+        # A and Z, each whole or by rows, A's face copy, and the sweeps' copy of one of them (room for all but F diagonals)
+        swept = v["nnzb"] - int((v["cf"] == 0).sum()) if v["sweep_nnzb"] >= 0 else 0
+        rect = v["face_rmax"] * v["face_cmax"]
+        most += 4 * (bb * (v["nnzb"] + v["z_vals"].shape[0] + v["nb"]) + rect * v["nnzb"] + (rect or bb) * swept)
+    _say(f"  float storage adds {(live['fp32'] - live['fp64']) / 2**20:.2f} MiB, at most {most / 2**20:.2f}")
+    assert live["fp32"] - live["fp64"] <= most
