@@ -967,10 +967,13 @@ __global__ __launch_bounds__(kThreads) void k_restrict(const int *__restrict__ z
 // under a condition would wait for qcol).  A 9 x 9 FP64 lane takes two rows at a
 // time, their loads before either product: 8% faster at Q2 N = 256; in FP32, and with
 // longer rows, the registers cost more than that gives.  PIN: the whole 25 x 25 FP64
-// row is loaded before its product, at three waves per SIMD: left to itself the
-// compiler keeps to more waves and waits for x's words one load at a time (103 us a
-// restriction at Q4 N = 512, against 82).  Where the caller's own registers are few
-// (the later sweeps, 29.5 us against 32) it does better alone.
+// row and the first kPin words of x are loaded before the product, which still leaves
+// four waves per SIMD (128 registers).  Restrictions of Q4 N = 512 on levels 0 / 1 / 2:
+// 83 / 92 / 112 us; with all of x's words first, at three waves, 95 / 99 / 120; left to
+// the compiler, which keeps to more waves and waits for x's words one load at a time,
+// 105 / 130 / 167.  Where the caller's own registers are few (the later sweeps, 29.5 us
+// against 32) it does better alone.
+constexpr int kPin = 8;
 template <int BS, bool NEG, bool PIN, typename MT, typename VT, typename AT>
 __device__ inline void stored_row_dots(const MT *__restrict__ vals, const VT *__restrict__ x, const int *qcol,
                                        double *dot, int v0, int v1, int bs, AT &&at) {
@@ -981,14 +984,16 @@ __device__ inline void stored_row_dots(const MT *__restrict__ vals, const VT *__
             const MT *blk = vals + at(v) * bs;
             const VT *xj = x + static_cast<int64_t>(NEG ? max(J, 0) : J) * bs;
             double d;
-            if constexpr (BS >= 25 && sizeof(MT) == 8 && PIN) {   // (every load before the first product)
+            if constexpr (BS >= 25 && sizeof(MT) == 8 && PIN) {
                 MT a[BS];
                 VT b[BS];
 #pragma unroll
                 for (int c = 0; c < BS; ++c) a[c] = blk[c];
 #pragma unroll
-                for (int c = 0; c < BS; ++c) b[c] = xj[c];
+                for (int c = 0; c < kPin; ++c) b[c] = xj[c];
                 __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int c = kPin; c < BS; ++c) b[c] = xj[c];
                 d = block_row_dot<BS>(a, b, BS);
             } else {
                 d = block_row_dot<BS>(blk, xj, bs);
