@@ -495,9 +495,11 @@ struct SplitCopy {
 // Class of each F row (depth, cut at 2) and the F list in descending depth:
 // flist is replaced; counts (device, 2 ints) receives {n2, n1}.
 void order_by_depth(const DevBSR &A, const int8_t *cf, DBuf<int> &flist, int nF, int *counts, hipStream_t s);
+// Whether a split copy of nF rows of A keeps int32 offsets: face rectangles do, whole
+// rows while all blocks but nF hold at most INT_MAX entries.
+bool split_fits(const DevBSR &A, const FaceCopy &F, int nF);
 // Build S from A (and its face copy F when F.on), the depth-ordered F list and
-// its counts; amask as for build_sweep.  S.on stays false when the kept rows
-// exceed int32 offsets.
+// its counts; amask as for build_sweep.  For levels that split_fits takes.
 void build_split(const DevBSR &A, const FaceCopy &F, const double *dinv, const int8_t *cf, const int *pmap,
                  const int *flist, int nF, int n1, int n2, SplitCopy &S, hipStream_t s, const uint32_t *amask);
 void split_to_float(SplitCopy &S, int bs, hipStream_t s);

@@ -532,11 +532,12 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
 
 void build_sweeps(Hier &h, bool trans, hipStream_t s) {
     if (h.prm.sweep_copy == 0) return;
-    // the large levels' forward sweeps read split copies: their F lists in order of depth first
+    // the large levels' forward sweeps read split copies: their F lists in order of depth first.  (A level
+    // whose copy would not fit keeps its list and sweeps A itself, as without copies.)
     if (!trans) {
         std::vector<Level *> lv;
         for (auto &Lp : h.lv)
-            if (!Lp->coarsest && Lp->nF > 0 && Lp->nF <= INT_MAX / 3 && !few_lanes(Lp->A.nb, Lp->A.bs))
+            if (!Lp->coarsest && split_fits(Lp->A, Lp->face, Lp->nF) && !few_lanes(Lp->A.nb, Lp->A.bs))
                 lv.push_back(Lp.get());
         if (!lv.empty()) {
             DBuf<int> counts(2 * lv.size());

@@ -341,11 +341,17 @@ void order_by_depth(const DevBSR &A, const int8_t *cf, DBuf<int> &flist, int nF,
     flist = std::move(out);
 }
 
+bool split_fits(const DevBSR &A, const FaceCopy &F, int nF) {
+    const int64_t bb = static_cast<int64_t>(A.bs) * A.bs;
+    return nF > 0 && nF <= INT_MAX / 3 && A.bs <= 32 &&
+           (F.on || std::max<int64_t>(A.nnzb - nF, 1) * bb <= INT_MAX);
+}
+
 void build_split(const DevBSR &A, const FaceCopy &F, const double *dinv, const int8_t *cf, const int *pmap,
                  const int *flist, int nF, int n1, int n2, SplitCopy &S, hipStream_t s, const uint32_t *amask) {
     S = SplitCopy();
     const int bs = A.bs;
-    if (nF <= 0 || bs > 32) return;
+    if (!split_fits(A, F, nF)) return;
     const bool face = F.on;
     S.nF = nF;
     S.n1 = n1;
@@ -380,10 +386,8 @@ void build_split(const DevBSR &A, const FaceCopy &F, const double *dinv, const i
         k_split_fill<false><<<grid, 256, 0, s>>>(A.rowptr.get(), A.colidx.get(), cf, pmap, nullptr, flist, nF, S.cap,
                                                  S.rowptr.get(), S.colidx.get(), S.ccol.get(), nullptr, src.get());
         NAIR_HIP(hipGetLastError());
-        if (!build_row_blocks(A.vals.get(), S.cap, bs, S.rows, s, src.get(), total, amask)) {
-            S = SplitCopy();
-            return;
-        }
+        if (!build_row_blocks(A.vals.get(), S.cap, bs, S.rows, s, src.get(), total, amask))
+            fail(NAIR_EDEVICE, "build_split: the level's rows exceed int32 offsets");
     }
     k_split_dinv<<<grid, 256, 0, s>>>(dinv, flist, nF, bs, S.rowptr.get(), face ? S.meta.get() : nullptr,
                                       S.rows.mask.get(), S.umask.get(), S.dinv.get());
