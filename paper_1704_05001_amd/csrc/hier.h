@@ -107,14 +107,14 @@ inline MatView<float> op_view32(const Level &L, bool trans) {
 
 inline SplitView<double> split_view(const Level &L) {
     const SplitCopy &S = L.split;
-    return SplitView<double>{L.flist.get(), S.nF, S.n1, S.rowptr.get(), S.colidx.get(), S.ccol.get(),
+    return SplitView<double>{S.flist.get(), S.nF, S.n1, S.rowptr.get(), S.colidx.get(), S.ccol.get(),
                              S.rc ? S.meta.get() : nullptr, S.vals.get(), S.cmax, S.rc,
                              RowBlockView<double>{S.rows.mask.get(), S.rows.off.get(), S.rows.vals.get()},
                              S.umask.get(), S.dinv.get(), S.s.get(), S.w.get()};
 }
 inline SplitView<float> split_view32(const Level &L) {
     const SplitCopy &S = L.split;
-    return SplitView<float>{L.flist.get(), S.nF, S.n1, S.rowptr.get(), S.colidx.get(), S.ccol.get(),
+    return SplitView<float>{S.flist.get(), S.nF, S.n1, S.rowptr.get(), S.colidx.get(), S.ccol.get(),
                             S.rc ? S.meta.get() : nullptr, S.vals32.get(), S.cmax, S.rc,
                             RowBlockView<float>{S.rows.mask.get(), S.rows.off.get(), S.rows.vals32.get()},
                             S.umask.get(), S.dinv.get(), S.s.get(), S.w.get()};

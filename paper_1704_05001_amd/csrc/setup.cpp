@@ -532,8 +532,8 @@ void build_hierarchy(Hier &h, int nsys, const int *sys_nb, int nb, int bs, const
 
 void build_sweeps(Hier &h, bool trans, hipStream_t s) {
     if (h.prm.sweep_copy == 0) return;
-    // the large levels' forward sweeps read split copies: their F lists in order of depth first.  (A level
-    // whose copy would not fit keeps its list and sweeps A itself, as without copies.)
+    // the large levels' forward sweeps read split copies: their lists of F rows in order of depth first.  (A
+    // level whose copy would not fit sweeps A itself, as without copies.)
     if (!trans) {
         std::vector<Level *> lv;
         for (auto &Lp : h.lv)
@@ -541,14 +541,16 @@ void build_sweeps(Hier &h, bool trans, hipStream_t s) {
                 lv.push_back(Lp.get());
         if (!lv.empty()) {
             DBuf<int> counts(2 * lv.size());
+            std::vector<DBuf<int>> lists;
             for (size_t k = 0; k < lv.size(); ++k)
-                order_by_depth(lv[k]->A, lv[k]->cf.get(), lv[k]->flist, lv[k]->nF, counts.get() + 2 * k, s);
+                lists.push_back(order_by_depth(lv[k]->A, lv[k]->cf.get(), lv[k]->flist.get(), lv[k]->nF,
+                                               counts.get() + 2 * k, s));
             std::vector<int> hc(2 * lv.size());
             read_ints(counts.get(), hc.data(), static_cast<int>(hc.size()), s);
             for (size_t k = 0; k < lv.size(); ++k) {
                 Level &L = *lv[k];
-                build_split(L.A, L.face, L.dinv.get(), L.cf.get(), L.pmap.get(), L.flist.get(), L.nF, hc[2 * k + 1],
-                            hc[2 * k], L.split, s, L.amask.get());
+                build_split(L.A, L.face, L.dinv.get(), L.cf.get(), L.pmap.get(), std::move(lists[k]), L.nF,
+                            hc[2 * k + 1], hc[2 * k], L.split, s, L.amask.get());
             }
         }
     }

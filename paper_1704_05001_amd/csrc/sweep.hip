@@ -330,15 +330,15 @@ void build_short_rows(const DevBSR &A, const DevBSR &Z, const int *flist, int nF
     S.on = true;
 }
 
-void order_by_depth(const DevBSR &A, const int8_t *cf, DBuf<int> &flist, int nF, int *counts, hipStream_t s) {
+DBuf<int> order_by_depth(const DevBSR &A, const int8_t *cf, const int *flist, int nF, int *counts, hipStream_t s) {
     DBuf<int> flag(static_cast<size_t>(nF) * 3), pos(static_cast<size_t>(nF) * 3 + 1), out(static_cast<size_t>(nF));
     const unsigned grid = grid_for(nF, 256);
-    k_depth_class<<<grid, 256, 0, s>>>(A.rowptr.get(), A.colidx.get(), cf, flist.get(), nF, flag.get());
+    k_depth_class<<<grid, 256, 0, s>>>(A.rowptr.get(), A.colidx.get(), cf, flist, nF, flag.get());
     NAIR_HIP(hipGetLastError());
     scan_exclusive(flag.get(), pos.get(), 3 * nF, s);
-    k_depth_place<<<grid, 256, 0, s>>>(flist.get(), flag.get(), pos.get(), nF, out.get(), counts);
+    k_depth_place<<<grid, 256, 0, s>>>(flist, flag.get(), pos.get(), nF, out.get(), counts);
     NAIR_HIP(hipGetLastError());
-    flist = std::move(out);
+    return out;
 }
 
 bool split_fits(const DevBSR &A, const FaceCopy &F, int nF) {
@@ -348,11 +348,13 @@ bool split_fits(const DevBSR &A, const FaceCopy &F, int nF) {
 }
 
 void build_split(const DevBSR &A, const FaceCopy &F, const double *dinv, const int8_t *cf, const int *pmap,
-                 const int *flist, int nF, int n1, int n2, SplitCopy &S, hipStream_t s, const uint32_t *amask) {
+                 DBuf<int> &&list, int nF, int n1, int n2, SplitCopy &S, hipStream_t s, const uint32_t *amask) {
     S = SplitCopy();
     const int bs = A.bs;
     if (!split_fits(A, F, nF)) return;
     const bool face = F.on;
+    S.flist = std::move(list);
+    const int *flist = S.flist.get();
     S.nF = nF;
     S.n1 = n1;
     S.n2 = n2;
