@@ -116,11 +116,15 @@ typedef struct {
                                  the depth of their F-F couplings, with D_F^{-1} in the same order:
                                  the Jacobi F sweeps read that contiguously, the later ones of a
                                  visit only what still changes (and a copy in F-list order of the
-                                 finest A^T once a transposed solve needs it); 0: no copies; 1: every
-                                 level that relaxes.  The sweep computes D_I^{-1}(r_I - sum_{J != I} A_IJ e_J)
-                                 either way; with one lane group per row (nair_params.tuning) the
-                                 results are bit-identical with and without copies.  Costs about
-                                 the F rows' share of each selected operator in memory. */
+                                 finest A^T once a transposed solve needs it); 0: no copies of values;
+                                 1: every level that relaxes (those that a collapsed coarse cycle
+                                 stands for too, where no cycle reads them).  With -1 and 0 the smaller
+                                 levels keep the first 16 columns of their F rows and of Z's rows
+                                 beside a header (144 and 80 bytes a row).  The sweep computes
+                                 D_I^{-1}(r_I - sum_{J != I} A_IJ e_J) either way; with one lane
+                                 group per row (nair_params.tuning) the results are bit-identical
+                                 with and without copies.  Costs about the F rows' share of each
+                                 selected operator in memory. */
     int32_t matrix_cores;     /* 1 (default): the setup's dense block products (Neumann products,
                                  T = -D^-1 A_ff, Z = -S D^-1 and the Galerkin blocks) of 9x9, 16x16
                                  and 25x25 blocks run on the FP64 matrix cores; 0: on the vector
@@ -329,7 +333,10 @@ nair_status nair_history(nair_hier h, double *buf, int32_t cap, int32_t *n);
 
 /* Hierarchy statistics (host outputs; per-level arrays hold up to 64 entries;
  * any pointer may be NULL).  oc/cc: operator and cycle complexity in work
- * units of one level-0 SpMV (section 6). */
+ * units of one level-0 SpMV (section 6).  Both count the method's levels and
+ * sweeps: a collapsed coarse cycle (nair_setup) counts as the levels that its
+ * matrix stands for, although the product reads n^2 entries, (n / bs)^2 blocks' worth,
+ * which for a small problem is more than its finest operator holds. */
 nair_status nair_info(nair_hier h, int32_t *levels, int32_t *nb_per_level, int64_t *nnzb_per_level,
                       double *oc, double *cc);
 

@@ -220,9 +220,10 @@ namespace {
 
 // Small device-to-host reads go through one pinned staging buffer.  A few words
 // (counts, flags, norms: nearly every read) are gathered into it by one kernel,
-// which ends by storing a ticket that the host polls: a copy command per item and
-// the stream's completion signal took 8 us each and 10 us (about 30 reads a setup,
-// a quarter of a small problem's).  Larger reads are copied and waited for.
+// which ends by storing a ticket that the host polls.  Behind a short kernel a read of
+// one, two or three items takes 14.7, 17.7 or 20.2 us by copies and the stream's
+// completion signal, 9.9 us this way (about 30 reads a setup).  Larger reads are
+// copied and waited for.
 constexpr size_t kStageBytes = 64 * 1024;
 constexpr size_t kGatherBytes = 4096;
 
