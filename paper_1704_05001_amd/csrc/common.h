@@ -475,7 +475,8 @@ void sweep_to_float(SweepCopy &S, int bs, hipStream_t s);
 // Q4, 512 x 512 cells, three sweeps: 36% / 14% of level 0's F rows have depth >=
 // 1 / 2 (70% / 52% on level 1, 80-90% below), 9 of 25 columns are in U_I; the
 // interpolation and the sweeps of the 8 levels went from 2.01 to 1.33 ms per
-// iteration against sweeps that read every row whole.  Levels below kFewLanes
+// iteration against sweeps that read every row whole (1.22 ms for the nine levels
+// since).  Levels below kFewLanes
 // lanes are bound by launches and latency and keep the plain sweeps.
 struct SplitCopy {
     bool on = false;
